@@ -105,6 +105,13 @@ __host__ __device__ inline int64_t blocked_index(int64_t n, int64_t k, int64_t K
 // for the float32 store, the exposed operator).
 hipError_t launch_gemm_bf16(const uint16_t* A, const uint16_t* B, int M, int N_pad, int K,
                             const EpiArgs& e, hipStream_t s, bool blocked_b = true);
+// The same product on smaller tiles (gemm_bf16_tiles.hip; B in MFMA blocks),
+// and the tile launch_gemm_bf16 takes for a shape.  k32x32 has no EPI_HEAD,
+// k256x128 only that.
+enum class GemmTile { k32x32, k64x64, k128x64, k128x128, k256x128, k256x256 };
+GemmTile pick_gemm_tile(int kind, int M, int N_pad, int K);
+hipError_t launch_gemm_bf16_tiles(GemmTile t, const uint16_t* A, const uint16_t* B, int M, int N_pad, int K,
+                                  const EpiArgs& e, hipStream_t s);
 hipError_t launch_gemm_f32(const float* A, const float* B, int M, int N_pad, int K,
                            const EpiArgs& e, hipStream_t s);
 // Decoding step: M <= 32 rows, each output element accumulated exactly as

@@ -58,54 +58,22 @@
 // row-grouped tile order (4 row tiles per group, 8 when the ring holds B),
 // which keeps the A and B panels the co-resident workgroups of an XCD share
 // in that XCD's L2.
-#include "epilogue.h"
+#include "gemm_tile.h"
 
 namespace lmgc {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
 constexpr int BM = 256, BN = 256, BK = 64;
 constexpr int kThreads = 256;
 // row tiles per group of the tile order: 4 when the ring holds A, 8 when it
 // holds B (measured best at the 7B shape)
 constexpr int kGroupM = 4, kGroupMB = 8;
-constexpr int kXcds = 8;
 // MFMAs of a stage that follow its barrier
 constexpr int kAfterBarrier = 32;
-// s_waitcnt immediates: vmcnt(n) with expcnt and lgkmcnt at their maxima
-// (vmcnt bits 3:0 and 15:14), and lgkmcnt(0) alone
-constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0xF70; }
+// s_waitcnt immediate: lgkmcnt(0) alone
 constexpr int kLgkm0 = 0xC07F;
 
 __device__ inline int slot(int row, int chunk) { return row * 8 + (chunk ^ ((row >> 1) & 7)); }
-
-__device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-template <int GM>
-__device__ inline bool map_tile(int bid, int nblocks, int ntm, int ntn, int& tm, int& tn) {
-  const int total = ntm * ntn;
-  const int per = nblocks / kXcds;  // nblocks is a multiple of kXcds
-  const int t = (bid % kXcds) * per + bid / kXcds;
-  if (t >= total) return false;
-  const int in_group = GM * ntn;
-  const int g = t / in_group;
-  const int first = g * GM;
-  const int gs = min(ntm - first, GM);
-  const int r = t - g * in_group;
-  tm = first + r % gs;
-  tn = r / gs;
-  return true;
-}
-
-// Raw buffer resource (gfx9 layout: stride 0, dword 3 = 0x00020000) over
-// `bytes` bytes at p; loads at offsets >= bytes return zero.
-__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, int bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
-}
 
 template <int KIND, int HD, bool RB, bool BLKB>
 __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_kernel(
@@ -886,8 +854,12 @@ hipError_t launch_gemm_bf16(const uint16_t* A, const uint16_t* B, int M, int N_p
                             const EpiArgs& e, hipStream_t s, bool blocked_b) {
   if (M <= 0) return hipSuccess;
   if (e.step || K % BK != 0 || N_pad % BN != 0) return hipErrorInvalidValue;
-  const int ntm = (M + BM - 1) / BM, ntn = N_pad / BN;
   const bool qkv = e.kind == EPI_QKV_ROPE || e.kind == EPI_QKV_BIAS;
+  if (blocked_b && (!qkv || e.hd == 128 || e.hd == 64)) {
+    const GemmTile t = pick_gemm_tile(e.kind, M, N_pad, K);
+    if (t != GemmTile::k256x256) return launch_gemm_bf16_tiles(t, A, B, M, N_pad, K, e, s);
+  }
+  const int ntm = (M + BM - 1) / BM, ntn = N_pad / BN;
   if (qkv && e.hd == 128) return launch_kind<128>(A, B, M, K, ntm, ntn, e, s, blocked_b);
   if (qkv && e.hd == 64) return launch_kind<64>(A, B, M, K, ntm, ntn, e, s, blocked_b);
   if (qkv) return hipErrorInvalidValue;
