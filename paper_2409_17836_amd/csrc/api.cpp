@@ -443,11 +443,11 @@ struct FwdBufs {
 
 // The decoder over B windows of W tokens.  dpos < 0: all W positions of each
 // window (rows b*W + j; tok is [B, W]).  dpos >= 0: one decoding step, the
-// row of position dpos of each window (rows b; tok[b] is the token at
-// dpos - 1; layers read K and V of earlier positions from the cache and add
-// their own).  Every kernel computes a row exactly as in the full pass, so
+// row of position dpos of each window (rows b; tok[b * ld] is the token at
+// dpos - 1, and row b * ld of cdf and logp takes the tables; layers read K and
+// V of earlier positions from the cache and add their own).  Every kernel computes a row exactly as in the full pass, so
 // the step's tables equal the full pass's row dpos bit for bit.
-static int forward(const lmgc_model* m, const int32_t* tok, int B, int W, int dpos, const lmgc_serial_params* p,
+static int forward(const lmgc_model* m, const int32_t* tok, int64_t ld, int B, int W, int dpos, const lmgc_serial_params* p,
                    uint32_t total, const FwdBufs& f, uint32_t* cdf, float* logp, hipStream_t s) {
   const lmgc_model_config& c = m->cfg;
   const bool step = dpos >= 0;
@@ -463,7 +463,7 @@ static int forward(const lmgc_model* m, const int32_t* tok, int B, int W, int dp
   };
   {
     ScopedTimer t(LMGC_K_EMBED, s);
-    HIP_OK(launch_embed(tok, B, W, p->bos_id, m->tok_emb, m->pos_emb, d, c.vocab, c.dtype, dpos, f.h, s));
+    HIP_OK(launch_embed(tok, ld, B, W, p->bos_id, m->tok_emb, m->pos_emb, d, c.vocab, c.dtype, dpos, f.h, s));
   }
   for (int l = 0; l < c.n_layers; l++) {
     const Layer& L = m->layers[l];
@@ -573,8 +573,8 @@ static int forward(const lmgc_model* m, const int32_t* tok, int B, int W, int dp
   }
   {
     ScopedTimer t(LMGC_K_LSE_CDF, s);
-    HIP_OK(launch_head_tables(f.part, m->v_pad / 64, f.za, LMGC_NALPHA_MAX, M, na, total, p->renorm, cdf,
-                              logp, s));
+    HIP_OK(launch_head_tables(f.part, m->v_pad / 64, f.za, LMGC_NALPHA_MAX, M, na, total, p->renorm,
+                              step ? ld : 1, cdf, logp, s));
   }
   return LMGC_OK;
 }
@@ -596,7 +596,7 @@ static int run_probs(const lmgc_model* m, const int32_t* tok, int B, int W, cons
 
   std::vector<void*> kc(c.n_layers, w.k), vc(c.n_layers, w.v);
   const FwdBufs f = {w.h, w.a, w.q, w.o, w.ff, w.za, w.part, w.head_alpha, kc.data(), vc.data()};
-  return forward(m, tok, B, W, -1, p, total, f, cdf, logp, s);
+  return forward(m, tok, 1, B, W, -1, p, total, f, cdf, logp, s);
 }
 
 static double probs_flops(const lmgc_model* m, int B, int W, int kind) {
@@ -629,7 +629,6 @@ struct StepWs {
   void* head_alpha;  // [tile, d] alphabet rows of the LM head (renormalised tables)
   int32_t* tok;     // [B] input token of the step (the previous position's)
   uint32_t* cdf;    // [B, A + 2] (A: alphabet size)
-  float* logp;      // [B, A]
   char* zero_from;  // q and the caches: cleared for every window group
   size_t zero_bytes, bytes;
   std::vector<void*> kc, vc;
@@ -654,7 +653,6 @@ static StepWs carve_step(const lmgc_model* m, int B, int W, char* base) {
   w.head_alpha = take((size_t)m->tile * c.d_model * act);
   w.tok = (int32_t*)take((size_t)B * 4);
   w.cdf = (uint32_t*)take((size_t)B * (LMGC_NSYM_MAX + 1) * 4);
-  w.logp = (float*)take((size_t)B * LMGC_NALPHA_MAX * 4);
   const size_t z0 = off;
   w.q = take((size_t)B * W * hq * act);
   for (int l = 0; l < c.n_layers; l++) {
@@ -678,12 +676,12 @@ static int check_step(const lmgc_model* m, int B, int W, const lmgc_serial_param
   return LMGC_OK;
 }
 
-// One decoding step at position j of every window of the group (w.tok holds
-// the tokens at j - 1); tables land in w.cdf (and w.logp).
-static int run_step(const lmgc_model* m, StepWs& w, int B, int W, int j, const lmgc_serial_params* p,
-                    uint32_t total, bool want_logp, hipStream_t s) {
+// One decoding step at position j of every window of the group: window b's
+// token at j - 1 is tok[b * ld], its tables go to row b * ld of cdf (and logp).
+static int run_step(const lmgc_model* m, StepWs& w, const int32_t* tok, int64_t ld, int B, int W, int j,
+                    const lmgc_serial_params* p, uint32_t total, uint32_t* cdf, float* logp, hipStream_t s) {
   const FwdBufs f = {w.h, w.a, w.q, w.o, w.ff, w.za, w.part, w.head_alpha, w.kc.data(), w.vc.data()};
-  return forward(m, w.tok, B, W, j, p, total, f, w.cdf, want_logp ? w.logp : nullptr, s);
+  return forward(m, tok, ld, B, W, j, p, total, f, cdf, logp, s);
 }
 
 // lmgc_probs computed one position at a time through the cache, with the
@@ -699,13 +697,10 @@ static int run_stepwise(const lmgc_model* m, const int32_t* tok, int B, int W, c
   const size_t na = alphabet(*p, ids), tw = na + 2;  // alphabet, table width
   HIP_OK(hipMemsetAsync(w.zero_from, 0, w.zero_bytes, s));
   for (int j = 0; j < W; j++) {
-    if (j > 0) HIP_OK(hipMemcpy2DAsync(w.tok, 4, tok + (j - 1), (size_t)W * 4, 4, B, hipMemcpyDeviceToDevice, s));
-    if ((rc = run_step(m, w, B, W, j, p, total, logp != nullptr, s))) return rc;
-    HIP_OK(hipMemcpy2DAsync(cdf + (size_t)j * tw, (size_t)W * tw * 4, w.cdf, tw * 4, tw * 4, B,
-                            hipMemcpyDeviceToDevice, s));
-    if (logp)
-      HIP_OK(hipMemcpy2DAsync(logp + (size_t)j * na, (size_t)W * na * 4, w.logp, na * 4, na * 4, B,
-                              hipMemcpyDeviceToDevice, s));
+    // position j of every window, straight from and to the callers' [B, W, ..]
+    if ((rc = run_step(m, w, tok + std::max(j - 1, 0), W, B, W, j, p, total, cdf + (size_t)j * tw,
+                       logp ? logp + (size_t)j * na : nullptr, s)))
+      return rc;
   }
   return LMGC_OK;
 }
@@ -876,7 +871,7 @@ static int decode(const lmgc_model* m, const uint8_t* buf, size_t bytes, int32_t
     }
     HIP_OK(hipMemsetAsync(sw.zero_from, 0, sw.zero_bytes, s));
     for (int j = 0; j < maxlen; j++) {
-      if ((rc = run_step(m, sw, nb, W, j, &h.p, h.total, false, s))) return rc;
+      if ((rc = run_step(m, sw, sw.tok, 1, nb, W, j, &h.p, h.total, sw.cdf, nullptr, s))) return rc;
       HIP_OK(hipMemcpyAsync(rows.data(), sw.cdf, (size_t)nb * (nsym + 1) * 4, hipMemcpyDeviceToHost, s));
       HIP_OK(hipStreamSynchronize(s));
       for (int i = 0; i < nb; i++) {

@@ -81,8 +81,8 @@ hipError_t launch_serialize(const void* values, int64_t n_values, const lmgc_ser
 // Token ids outside [0, vocab) are clamped (callers validate them).
 // dpos < 0: rows b*W + j of B whole windows (token of row j is BOS for j = 0,
 // else tokens[b, j-1]); dpos >= 0: row b is window b at position dpos, whose
-// input token is BOS for dpos = 0, else tokens[b].
-hipError_t launch_embed(const int32_t* tokens, int B, int W, int bos_id, const void* tok_emb,
+// input token is BOS for dpos = 0, else tokens[b * ld_tok].
+hipError_t launch_embed(const int32_t* tokens, int64_t ld_tok, int B, int W, int bos_id, const void* tok_emb,
                         const void* pos_emb, int d, int vocab, int dtype, int dpos, float* h,
                         hipStream_t s);
 
@@ -134,9 +134,10 @@ hipError_t launch_attention_f32(const float* q, const float* k, const float* v, 
 // logits.  -> cdf [M, A + 2], logp [M, A] (nullable).  renorm: the tables
 // are renormalised over the alphabet (the log-sum-exp runs over za alone,
 // part is not read); otherwise full-vocabulary tables with an escape bin.
+// Row r's outputs are row r * ld_out of cdf and logp.
 hipError_t launch_head_tables(const float2* part, int ngroups, const float* za, int ld_za, int M,
-                              int n_alpha, uint32_t total, int renorm, uint32_t* cdf, float* logp,
-                              hipStream_t s);
+                              int n_alpha, uint32_t total, int renorm, int64_t ld_out, uint32_t* cdf,
+                              float* logp, hipStream_t s);
 
 // dst [rows, cols]: row r < n_alpha = head row alpha_ids[r] (host array),
 // the remaining rows zero.  Rows are cols * elem_bytes bytes (multiple of 4).

@@ -47,11 +47,12 @@ def test_values(M, N, K):
     np.testing.assert_allclose(got.cpu().numpy(), ref, rtol=1e-5, atol=2e-4 * np.sqrt(K))
 
 
-@pytest.mark.parametrize("arch,heads,kv,d,vocab", [("gpt2", 4, 4, 256, 1000), ("llama", 2, 1, 256, 777),
-                                                  ("llama", 8, 2, 512, 5003)])
+@pytest.mark.parametrize("arch,heads,kv,d,vocab", [("gpt2", 8, 8, 512, 1000), ("llama", 2, 1, 256, 777),
+                                                  ("llama", 16, 4, 1024, 5003)])
 def test_tables_do_not_depend_on_the_batch(arch, heads, kv, d, vocab):
     """One window alone against the same window in a batch, through every
-    product of a decoder (QKV, residual, FFN, head), whole and ragged windows."""
+    product of a decoder (QKV, residual, FFN, head) and the norms of few and
+    of many rows, whole and ragged windows."""
     import torch
     shape = ModelShape(arch=arch, dtype="bf16", n_layers=2, d_model=d, n_heads=heads, n_kv_heads=kv, d_ff=2 * d,
                        vocab=vocab, max_pos=1024)
