@@ -580,64 +580,90 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_kernel(
   else epilogue(std::false_type{});
 }
 
-// Decoding step (M <= 32 rows: one row per window).  Every wave accumulates
-// one 16-column block for NRB blocks of 16 rows (NRB = 1 for M <= 16, else
-// 2; both row blocks take the same weight fragment) and runs, for every
-// output element, the same chain as gemm_bf16_kernel: 16x16x32 bf16 MFMAs
-// over the 32-wide k chunks in increasing order, lane l holding row (l & 15)
-// of its row block and k values 8*(l >> 4) .. +8 of a chunk.  So a row's
-// outputs equal, bit for bit, what the tiled kernel gives that row in a batch
-// of whole windows.  Operands come straight from global memory (the step
-// streams the weights once), kRowsPf chunks ahead (fewer with two row
-// blocks, for registers).  The step is bound by how many weight bytes each
-// wave has in flight, so the waves are spread over as many CUs as the
-// epilogue allows.  NWR waves per workgroup:
-//  - 4: 64 columns; waves 2 and 3 hand their accumulators to waves 0 and 1
-//    through LDS, which run the epilogue on the (col, col + 32) pairs (QKV:
-//    the RoPE pairs and the transposed V stores);
-//  - 2: the two blocks c and c + 32 of one pair (gate/up, GELU, float32
-//    store);
-//  - 1: one block, for the residual add, which pairs nothing (N = d = 4096 has
-//    only 256 blocks: one wave on each CU instead of 64 four-wave groups).
-constexpr int kRowsPf = 16;
+// Decoding step (M <= 32 rows: one row per window).  Every wave (a workgroup
+// of its own) accumulates NB 16-column blocks for NRB blocks of 16 rows (NRB =
+// 1 for M <= 16, else 2) and runs, for every output element, the same chain
+// as gemm_bf16_kernel: 16x16x32 bf16 MFMAs over the 32-wide k chunks in
+// increasing order, lane l holding row (l & 15) of its row block and k values
+// 8*(l >> 4) .. +8 of a chunk.  So a row's outputs equal, bit for bit, what
+// the tiled kernels give that row in a batch of whole windows.  Operands come
+// straight from global memory, PF chunks ahead: the weights once per step,
+// non-temporal (they displace the activations and the K/V cache otherwise:
+// 5 to 14 % of a launch), the activation rows from L2 by every wave.
+// NB: 1 for the residual add (N = d = 4096 has only 256 blocks: one wave on
+// each CU); 2 for the kinds that pair columns c and c + 32 and for the
+// float32 store; 4, a whole 64-column group, for the head.  So a wave's
+// activation fragments serve all its blocks and the epilogue finds its
+// columns in the wave's own registers.  Against four waves of one block each
+// (two for the paired kinds) that hand their columns over through LDS, cold
+// weights, M = 8 / 32 rows: 7B QKV 24.1 / 39.8 -> 21.8 / 33.2 us, gate/up
+// 35.6 / 56.0 -> 30.7 / 40.5 (5.9 TB/s of weights at M = 8), O 10.3 / 14.9 ->
+// 9.2 / 13.1, down 21.5 / 32.8 -> 19.4 / 30.0, head 50.4 / 75.0 -> 47.6 /
+// 48.6; GPT-2 QKV 5.7 / 10.2 -> 4.6 / 6.7, head 18.6 / 29.7 -> 16.7 / 17.9.
+// With few waves (GPT-2's and TinyLlama's O and down) the bound is what one CU
+// pulls, about 40 GB/s of operands that miss its caches.
 constexpr int kRowsMax = 32;
 
-template <int KIND, int HD, int NWR, int NRB>
-__global__ __launch_bounds__(64 * NWR) void gemm_bf16_rows_kernel(const uint16_t* __restrict__ A,
-                                                                  const uint16_t* __restrict__ Bw,
-                                                                  int M, int K, EpiArgs e) {
-  constexpr int PF = NRB == 1 ? kRowsPf : 12;  // chunks in flight
-  // accumulators handed over: to the pair's first block (QKV: waves 2, 3 to
-  // 0, 1), or all to wave 0 (HEAD: waves 1..3, the group's blocks j = 1..3)
-  __shared__ f32x4 part[NWR == 4 ? 3 : 1][NRB][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int c;  // this wave's block
-  if (NWR == 4) c = blockIdx.x * 64 + wave * 16;
-  else if (NWR == 2) c = (blockIdx.x >> 1) * 64 + (blockIdx.x & 1) * 16 + wave * 32;
-  else c = blockIdx.x * 16;
-  const int r = lane & 15, kq = lane >> 4;
+template <int KIND, int HD, int NRB>
+__global__ __launch_bounds__(64) void gemm_bf16_rows_kernel(const uint16_t* __restrict__ A,
+                                                            const uint16_t* __restrict__ Bw, int M, int K,
+                                                            EpiArgs e) {
+  constexpr int NB = KIND == EPI_RESID ? 1 : KIND == EPI_HEAD ? 4 : 2;
+  // chunks in flight: 24 to 48 KB of loads per wave (a third less or a half
+  // more was no faster)
+  constexpr int PF = NB == 4 ? 8 : NB == 1 && NRB == 1 ? 16 : 12;
+  using E = Epi<uint16_t, KIND, HD>;
+  const int lane = threadIdx.x, r = lane & 15, kq = lane >> 4;
+  // first block of the wave; block j is cb + cstep * j
+  constexpr int cstep = NB == 2 ? 32 : 16;
+  const int cb = NB == 2 ? ((int)blockIdx.x >> 1) * 64 + (blockIdx.x & 1) * 16 : (int)blockIdx.x * 16 * NB;
+  const int col = cb + r;
   // rows past M re-read row M - 1; they only feed outputs that are not stored
   const u32x4* pa[NRB];
 #pragma unroll
   for (int rb = 0; rb < NRB; rb++)
     pa[rb] = reinterpret_cast<const u32x4*>(A + (int64_t)min(16 * rb + r, M - 1) * K + kq * 8);
-  // B in MFMA blocks: the wave's 16 rows are one contiguous stream of 1 KB
-  // blocks, lane l's 16 bytes at 16 l of each
+  // B in MFMA blocks: 16 columns are one contiguous stream of 1 KB blocks,
+  // lane l's 16 bytes at 16 l of each
   const int nkc = K / 32;  // A chunk kc starts at u32x4 index 4 * kc
-  const u32x4* pb = reinterpret_cast<const u32x4*>(Bw) + (int64_t)(c / 16) * nkc * 64 + lane;
-  f32x4 acc[NRB];
+  const u32x4* pb[NB];
 #pragma unroll
-  for (int rb = 0; rb < NRB; rb++) acc[rb] = f32x4{};
-  u32x4 fa[PF][NRB], fb[PF];
+  for (int j = 0; j < NB; j++)
+    pb[j] = reinterpret_cast<const u32x4*>(Bw) + (int64_t)((cb + cstep * j) / 16) * nkc * 64 + lane;
+  // the residual rows, fetched under the weight stream
+  float old[NB == 1 ? NRB : 1][4], bias = 0.f;
+  if constexpr (NB == 1) {
+    static_assert(KIND == EPI_RESID, "single blocks only for the residual add");
+    if (col < e.N) {
+      if (e.bias) bias = load_par<uint16_t>(e.bias, col);
+#pragma unroll
+      for (int rb = 0; rb < NRB; rb++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          const int row = 16 * rb + 4 * kq + i;
+          if (row < M) old[rb][i] = e.c[(int64_t)row * e.ldc + col];
+        }
+    }
+  }
+  f32x4 acc[NRB][NB];
+#pragma unroll
+  for (int rb = 0; rb < NRB; rb++)
+#pragma unroll
+    for (int j = 0; j < NB; j++) acc[rb][j] = f32x4{};
+  u32x4 fa[PF][NRB], fb[PF][NB];
   auto fetch = [&](int u, int kc) __attribute__((always_inline)) {
 #pragma unroll
     for (int rb = 0; rb < NRB; rb++) fa[u][rb] = pa[rb][4 * kc];
-    fb[u] = pb[(int64_t)kc * 64];
+#pragma unroll
+    for (int j = 0; j < NB; j++) fb[u][j] = __builtin_nontemporal_load(pb[j] + (int64_t)kc * 64);
   };
   auto mma = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
-    for (int rb = 0; rb < NRB; rb++)
-      acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fa[u][rb]), as_bf16x8(fb[u]), acc[rb], 0, 0, 0);
+    for (int j = 0; j < NB; j++)
+#pragma unroll
+      for (int rb = 0; rb < NRB; rb++)
+        acc[rb][j] =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fa[u][rb]), as_bf16x8(fb[u][j]), acc[rb][j], 0, 0, 0);
   };
   // chunk kc lives in slot kc % PF.  The steady loop consumes and refills
   // every slot without conditions (so the loads' wait counts stay exact);
@@ -669,29 +695,16 @@ __global__ __launch_bounds__(64 * NWR) void gemm_bf16_rows_kernel(const uint16_t
     }
   }
   // lane holds column c + (lane & 15) and rows 16 rb + 4 kq + i
-  using E = Epi<uint16_t, KIND, HD>;
-  const int col = c + r;
-  if constexpr (NWR == 1) {
-    static_assert(KIND == EPI_RESID, "single blocks only for the residual add");
+  if constexpr (KIND == EPI_RESID) {
     if (col >= e.N) return;
-    const float bias = e.bias ? load_par<uint16_t>(e.bias, col) : 0.f;
 #pragma unroll
     for (int rb = 0; rb < NRB; rb++)
 #pragma unroll
       for (int i = 0; i < 4; i++) {
         const int row = 16 * rb + 4 * kq + i;
-        if (row < M) {
-          float* p = e.c + (int64_t)row * e.ldc;
-          p[col] = resid_add(p[col], acc[rb][i], bias);
-        }
+        if (row < M) e.c[(int64_t)row * e.ldc + col] = resid_add(old[rb][i], acc[rb][0][i], bias);
       }
   } else if constexpr (KIND == EPI_HEAD) {
-    static_assert(NWR == 4, "the head's groups are 64 columns: four waves");
-#pragma unroll
-    for (int rb = 0; rb < NRB; rb++)
-      if (wave > 0) part[wave - 1][rb][lane] = acc[rb];
-    __syncthreads();
-    if (wave > 0) return;
     bool ok[4];
     int aidx[4];
 #pragma unroll
@@ -702,55 +715,34 @@ __global__ __launch_bounds__(64 * NWR) void gemm_bf16_rows_kernel(const uint16_t
     const bool any_alpha = __any(aidx[0] >= 0 || aidx[1] >= 0 || aidx[2] >= 0 || aidx[3] >= 0);
 #pragma unroll
     for (int rb = 0; rb < NRB; rb++) {
-      f32x4 blk[4];
-      blk[0] = acc[rb];
-#pragma unroll
-      for (int j = 1; j < 4; j++) blk[j] = part[j - 1][rb][lane];
       float z[4][4];
 #pragma unroll
       for (int i = 0; i < 4; i++)
 #pragma unroll
-        for (int j = 0; j < 4; j++) z[i][j] = ok[j] ? blk[j][i] : -INFINITY;
+        for (int j = 0; j < 4; j++) z[i][j] = ok[j] ? acc[rb][j][i] : -INFINITY;
       head_rows4(e, z, aidx, any_alpha, 16 * rb + 4 * kq, M, blockIdx.x, r);
     }
   } else {
-    constexpr int NH = NWR / 2;  // the second half of the waves hand over
-#pragma unroll
-    for (int rb = 0; rb < NRB; rb++)
-      if (wave >= NH) part[wave - NH][rb][lane] = acc[rb];
-    __syncthreads();
-    if (wave >= NH) return;
     const ColInfo ci = E::column(e, col);
 #pragma unroll
-    for (int rb = 0; rb < NRB; rb++) {
-      const f32x4 hi = part[wave][rb][lane];  // block c + 32, same lane layout
+    for (int rb = 0; rb < NRB; rb++)
 #pragma unroll
       for (int i = 0; i < 4; i++) {
         const int row = 16 * rb + 4 * kq + i;
-        if (row < M) E::row(e, ci, col, row, row, e.dpos, acc[rb][i], hi[i]);
+        if (row < M) E::row(e, ci, col, row, row, e.dpos, acc[rb][0][i], acc[rb][1][i]);
       }
-    }
   }
-}
-
-template <int KIND, int HD, int NRB>
-hipError_t launch_rows_nrb(const uint16_t* A, const uint16_t* B, int M, int N_pad, int K,
-                           const EpiArgs& e, hipStream_t s) {
-  if constexpr (KIND == EPI_RESID) {
-    hipLaunchKernelGGL((gemm_bf16_rows_kernel<KIND, HD, 1, NRB>), dim3(N_pad / 16), dim3(64), 0, s, A, B, M, K, e);
-  } else if constexpr (KIND == EPI_QKV_ROPE || KIND == EPI_QKV_BIAS || KIND == EPI_HEAD) {
-    hipLaunchKernelGGL((gemm_bf16_rows_kernel<KIND, HD, 4, NRB>), dim3(N_pad / 64), dim3(256), 0, s, A, B, M, K, e);
-  } else {
-    hipLaunchKernelGGL((gemm_bf16_rows_kernel<KIND, HD, 2, NRB>), dim3(N_pad / 32), dim3(128), 0, s, A, B, M, K, e);
-  }
-  return hipGetLastError();
 }
 
 template <int KIND, int HD>
 hipError_t launch_rows_one(const uint16_t* A, const uint16_t* B, int M, int N_pad, int K,
                            const EpiArgs& e, hipStream_t s) {
-  return M <= 16 ? launch_rows_nrb<KIND, HD, 1>(A, B, M, N_pad, K, e, s)
-                 : launch_rows_nrb<KIND, HD, 2>(A, B, M, N_pad, K, e, s);
+  const dim3 grid(N_pad / (KIND == EPI_RESID ? 16 : KIND == EPI_HEAD ? 64 : 32)), block(64);
+  if (M <= 16)
+    hipLaunchKernelGGL((gemm_bf16_rows_kernel<KIND, HD, 1>), grid, block, 0, s, A, B, M, K, e);
+  else
+    hipLaunchKernelGGL((gemm_bf16_rows_kernel<KIND, HD, 2>), grid, block, 0, s, A, B, M, K, e);
+  return hipGetLastError();
 }
 
 // HD != 0: the QKV kinds of a bf16 model with that head dim; HD == 0: the rest.
