@@ -169,8 +169,9 @@ int64_t lmgc_lossy_workspace(int64_t n_values);
  *   d_values (in place) but must not overlap it otherwise.
  *   k: number kept, 0 <= k; k >= n_values keeps everything.  The paper's
  *   "keep p percent" is k = floor(n_values * p / 100).
- * GPU, async on stream (a chain of small launches: four histogram passes,
- * a tie count and one ordered write).  Errors: EINVAL, ESIZE (workspace).
+ * GPU, async on stream (one launch for short vectors, else a chain: two
+ * counting passes and a write, and three more that only heavy ties need).
+ * Errors: EINVAL, ESIZE (workspace).
  */
 int lmgc_sparsify_topk(const float* d_values, int64_t n_values, int64_t k, float* d_out,
                        void* d_workspace, size_t workspace_bytes, void* stream);
@@ -201,8 +202,9 @@ int lmgc_sparsify_topk_noalloc(const float* d_values, int64_t n_values, int64_t 
  *   [n_values] for bits > 8.
  *   min_max: nullable host float[2]; receives (min, max), the values a
  *   receiver needs to map indices back.
- * Synchronises the stream once (min and max are read back to validate them)
- * and then enqueues the quantisation.  Errors: EINVAL (bad arguments, or the
+ * Synchronises the stream once, after the quantisation (min, max and the
+ * count of non-finite values are read back); with non-finite values d_indices
+ * is left as it was.  Errors: EINVAL (bad arguments, or the
  * vector holds a NaN or an infinity), ESIZE (workspace), EDEVICE.
  */
 int lmgc_quantize_linear(const float* d_values, int64_t n_values, int32_t bits, void* d_indices,

@@ -1040,15 +1040,15 @@ int lmgc_quantize_linear(const float* d_values, int64_t n_values, int32_t bits, 
   }
   if ((rc = check_lossy_ws(d_workspace, workspace_bytes))) return rc;
   hipStream_t s = (hipStream_t)stream;
-  LossyMinMax* slot = lossy_minmax_slot(d_workspace);
-  hipError_t e = launch_minmax(d_values, n_values, d_workspace, slot, s);
+  // the indices are computed before the read-back (their kernel finds min and
+  // max on the device), so the stream does not idle while the host validates
+  hipError_t e = launch_quantize_linear(d_values, n_values, bits, d_indices, d_workspace, s);
+  if (e != hipSuccess) return set_error(LMGC_EDEVICE, "quantize launch: %s", hipGetErrorString(e));
   LossyMinMax mm{};
-  if (e == hipSuccess) e = hipMemcpyAsync(&mm, slot, sizeof(mm), hipMemcpyDeviceToHost, s);
+  e = hipMemcpyAsync(&mm, lossy_minmax_slot(d_workspace), sizeof(mm), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return set_error(LMGC_EDEVICE, "quantize min/max: %s", hipGetErrorString(e));
   if (mm.nonfinite) return set_error(LMGC_EINVAL, "values hold %u NaN or infinite entries", mm.nonfinite);
-  e = launch_quantize_linear(d_values, n_values, bits, mm.mn, mm.mx, d_indices, s);
-  if (e != hipSuccess) return set_error(LMGC_EDEVICE, "quantize launch: %s", hipGetErrorString(e));
   if (min_max) {
     min_max[0] = mm.mn;
     min_max[1] = mm.mx;

@@ -145,8 +145,8 @@ hipError_t launch_head_tables(const float2* part, int ngroups, const float* za, 
 hipError_t launch_alpha_head(const void* head, const int32_t* alpha_ids, int n_alpha, int rows, int cols,
                              int elem_bytes, void* dst, hipStream_t s);
 
-// Lossy steps (lossy.hip).  The workspace holds the top-k select state, the
-// per-chunk tie counts and the min/max partials; its size does not depend on n.
+// Lossy steps (lossy.hip).  The workspace holds the top-k counts and
+// candidates, or the min/max partials; its size does not depend on n.
 struct LossyMinMax {
   float mn, mx;
   uint32_t nonfinite;  // values that are NaN or infinite
@@ -154,14 +154,13 @@ struct LossyMinMax {
 };
 size_t lossy_workspace_bytes();
 hipError_t launch_sparsify_topk(const float* v, int64_t n, int64_t k, float* out, void* ws, hipStream_t s);
-// Writes the vector's LossyMinMax to res (device memory, e.g. lossy_minmax_slot(ws)).
-hipError_t launch_minmax(const float* v, int64_t n, void* ws, LossyMinMax* res, hipStream_t s);
 LossyMinMax* lossy_minmax_slot(void* ws);
 // Address (on the current device) and size of the library-owned device
 // scratch that lmgc_sparsify_topk_noalloc uses in place of a workspace.
 hipError_t lossy_scratch(void** ptr, size_t* bytes);
-hipError_t launch_quantize_linear(const float* v, int64_t n, int bits, float mn, float mx, void* idx,
-                                  hipStream_t s);
+// Minimum, maximum and the indices; the vector's LossyMinMax ends up in
+// lossy_minmax_slot(ws).  A vector with non-finite values leaves idx as it is.
+hipError_t launch_quantize_linear(const float* v, int64_t n, int bits, void* idx, void* ws, hipStream_t s);
 hipError_t launch_sign_pack(const float* v, int64_t n, uint8_t* out, hipStream_t s);
 
 // dst[r, :] = srcs.p[idx[r] >> 28][(idx[r] & 0x0fffffff), :] for r < rows;

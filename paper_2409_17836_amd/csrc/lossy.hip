@@ -4,14 +4,18 @@
 // float32 vector and bound by HBM bandwidth.
 //
 // Top-k is a radix select on the magnitude key (the IEEE bits with the sign
-// cleared, an unsigned integer whose order is the order of |v| for numbers):
-// four passes build a 256-bin histogram of one key byte among the keys that
-// match the bytes chosen so far, and a one-block kernel picks the next byte,
-// so the threshold key T and the number of keys equal to T that are kept
-// never leave the device.  Keys above T are kept; among keys equal to T the
-// lowest indices are kept, which needs the count of such keys before each
-// element: a per-chunk count, then an ordered pass per chunk with a block
-// scan.
+// cleared, an unsigned integer whose order is the order of |v| for numbers).
+// Two passes count the keys' leading 12 bits and, among the keys that share
+// the threshold's, their next 11; no digit leaves the device: every block of
+// a later kernel finds them in the histograms by itself (a suffix scan of 24
+// KB, against a launch of its own).  The 23 bits known then settle all keys
+// but the few that share them (n / 70000 for smooth distributions), so the
+// third pass over the vector writes the output, collects those candidates,
+// and one block ranks them by key and index.  Vectors with more candidates
+// than the list holds (heavy ties) take the last 8 bits by a third counting
+// pass, and a per-chunk count of the threshold's ties before an ordered write
+// with a block scan: ties are kept in index order, lowest first.
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -20,15 +24,31 @@ namespace lmgc {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kGridStride = 1024;       // blocks of the grid-stride passes
-constexpr int kMaxChunks = 2048;        // ordered chunks of the write pass
+constexpr int kGridStride = 512;        // blocks of the min/max pass, whose partials each later block merges
 constexpr int kTile = kThreads * 4;     // elements per block iteration
+// top-k: digits of 12, 11 and 8 bits, blocks of 1024 threads
+constexpr int kTopkThreads = 1024, kTopkTile = kTopkThreads * 4;
+constexpr int kBinsA = 4096, kBinsB = 2048, kBinsC = 256;
+constexpr int kShiftA = 19, kShiftB = 8;
+constexpr int kMaxChunks = 1024;        // ordered chunks of the tie passes
+constexpr int kMaxCand = 1000;          // keys that share the 23-bit prefix
 
-struct TopkState {
-  uint32_t prefix;  // key bytes chosen so far
-  uint32_t mask;    // which bits of prefix are chosen
-  uint32_t need;    // keys still to keep among those matching prefix
-  uint32_t pad;
+// Scratch of a top-k call.  A and B are counted by the first two passes; the
+// candidate list and, with too many candidates, the last digit's counts and
+// the chunks' ties share the rest.
+struct TopkScratch {
+  uint32_t a[kBinsA];
+  uint32_t b[kBinsB];
+  uint32_t n_cand;
+  uint32_t prefix, need, count;  // of topk_split_kernel, for the kernels after it
+  uint32_t pad[12];
+  union {
+    uint64_t cand[kMaxCand];
+    struct {
+      uint32_t c[kBinsC];
+      uint32_t ties[kMaxChunks];
+    };
+  };
 };
 
 __device__ inline uint32_t mag_key(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
@@ -46,6 +66,24 @@ __device__ inline float4 load4(const float* __restrict__ v, int64_t i, int64_t n
   return make_float4(t[0], t[1], t[2], t[3]);
 }
 
+// Calls f(i, x, valid) for the groups of four elements i, i + stride, ... < n
+// (i a multiple of 4), the loads of four groups in flight at once.
+template <class F>
+__device__ inline void for_each4(const float* v, int64_t i, int64_t stride, int64_t n, F&& f) {
+  for (; i + 3 * stride + 4 <= n; i += 4 * stride) {
+    float4 x[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) x[u] = *reinterpret_cast<const float4*>(v + i + u * stride);
+#pragma unroll
+    for (int u = 0; u < 4; u++) f(i + u * stride, x[u], 4);
+  }
+  for (; i < n; i += stride) {
+    int valid;
+    const float4 x = load4(v, i, n, valid);
+    f(i, x, valid);
+  }
+}
+
 __device__ inline void store4(float* __restrict__ o, int64_t i, int valid, float4 x) {
   if (valid == 4) {
     *reinterpret_cast<float4*>(o + i) = x;
@@ -56,71 +94,170 @@ __device__ inline void store4(float* __restrict__ o, int64_t i, int valid, float
 }
 
 // ------------------------------------------------------------------ top-k
-__global__ void topk_init_kernel(TopkState* st, uint32_t* hist, uint32_t k) {
-  hist[threadIdx.x] = 0;
-  if (threadIdx.x == 0) *st = TopkState{0u, 0u, k, 0u};
-}
-
-__global__ __launch_bounds__(kThreads) void topk_hist_kernel(const float* __restrict__ v, int64_t n,
-                                                             const TopkState* __restrict__ st,
-                                                             uint32_t* __restrict__ hist, int shift) {
-  __shared__ uint32_t lh[256];
-  lh[threadIdx.x] = 0;
-  __syncthreads();
-  const uint32_t prefix = st->prefix, mask = st->mask;
-  const int64_t stride = (int64_t)gridDim.x * kThreads * 4;
-  for (int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4; i < n; i += stride) {
-    int valid;
-    const float4 x = load4(v, i, n, valid);
-    const float t[4] = {x.x, x.y, x.z, x.w};
+// The digit of the key that `need` keys (by magnitude, largest first) reach:
+// bin d with fewer than `need` keys in the bins above it and at least `need`
+// with its own.  Every thread of the block gets d, how many keys of bin d are
+// still needed, and its count.
+struct Digit {
+  uint32_t d, need, count;
+};
+template <int NB>
+__device__ inline Digit find_digit(const uint32_t* __restrict__ hist, uint32_t need) {
+  constexpr int PER = NB > kTopkThreads ? NB / kTopkThreads : 1, NW = kTopkThreads / 64;
+  __shared__ uint32_t wsum[NW];
+  __shared__ Digit res;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, b0 = threadIdx.x * PER;
+  uint32_t c[PER], own = 0;
 #pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const uint32_t key = mag_key(t[e]);
-      if (e < valid && (key & mask) == prefix) atomicAdd(&lh[(key >> shift) & 0xFFu], 1u);
-    }
+  for (int i = 0; i < PER; i++) {
+    c[i] = b0 + i < NB ? hist[b0 + i] : 0u;
+    own += c[i];
+  }
+  uint32_t suf = own;  // bins of this thread and of the wave's later ones
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_down(suf, d);
+    if (lane + d < 64) suf += y;
+  }
+  if (lane == 0) wsum[wave] = suf;
+  __syncthreads();
+  for (int w = wave + 1; w < NW; w++) suf += wsum[w];
+  uint32_t above = suf - own;
+#pragma unroll
+  for (int i = PER - 1; i >= 0; i--) {
+    if (above < need && above + c[i] >= need) res = Digit{(uint32_t)(b0 + i), need - above, c[i]};
+    above += c[i];
   }
   __syncthreads();
-  const uint32_t c = lh[threadIdx.x];
-  if (c) atomicAdd(&hist[threadIdx.x], c);
+  const Digit r = res;
+  __syncthreads();  // res and wsum may be used again
+  return r;
 }
 
-// One block of 256: bin b of the byte at `shift` is chosen so that fewer than
-// `need` matching keys lie in bins above b and at least `need` in bins >= b.
-// The histogram is cleared for the next pass.
-__global__ __launch_bounds__(kThreads) void topk_select_kernel(TopkState* st, uint32_t* hist, int shift) {
-  __shared__ uint32_t suf[257];
-  const int t = threadIdx.x;
-  suf[t] = hist[t];
-  hist[t] = 0;
-  if (t == 0) suf[256] = 0;
+// The threshold's leading 23 bits, the keys still to keep among those that
+// share them, and how many share them.
+__device__ inline Digit find_prefix(const TopkScratch* __restrict__ sc, uint32_t k) {
+  const Digit a = find_digit<kBinsA>(sc->a, k);
+  const Digit b = find_digit<kBinsB>(sc->b, a.need);
+  return Digit{(a.d << (kShiftA - kShiftB)) | b.d, b.need, b.count};
+}
+
+__global__ __launch_bounds__(kTopkThreads) void topk_init_kernel(TopkScratch* sc) {
+  for (int i = threadIdx.x; i < kBinsA; i += kTopkThreads) sc->a[i] = 0;
+  for (int i = threadIdx.x; i < kBinsB; i += kTopkThreads) sc->b[i] = 0;
+  if (threadIdx.x == 0) sc->n_cand = 0;
+}
+
+// Adds the block's elements to hist: keys whose bits above `top` equal prefix
+// (all of them if top == 32), by their NB-valued digit at `shift`.
+template <int NB>
+__device__ inline void count_keys(const float* __restrict__ v, int64_t n, int top, uint32_t prefix, int shift,
+                                  uint32_t* __restrict__ hist) {
+  __shared__ uint32_t lh[NB];
+  for (int i = threadIdx.x; i < NB; i += kTopkThreads) lh[i] = 0;
   __syncthreads();
-  // inclusive suffix sums: suf[t] = sum of bins t..255
-  for (int d = 1; d < 256; d <<= 1) {
-    const uint32_t add = (t + d < 256) ? suf[t + d] : 0u;
-    __syncthreads();
-    suf[t] += add;
-    __syncthreads();
-  }
-  const uint32_t need = st->need;
+  // zeros (whole runs of them in sparse vectors, whose LDS atomics would all
+  // meet at one address) are counted in a register
+  uint32_t zeros = 0;
+  const int64_t stride = (int64_t)gridDim.x * kTopkTile;
+  for_each4(v, ((int64_t)blockIdx.x * kTopkThreads + threadIdx.x) * 4, stride, n,
+            [&](int64_t, float4 x, int valid) __attribute__((always_inline)) {
+              const float t[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+              for (int e = 0; e < 4; e++) {
+                const uint32_t key = mag_key(t[e]);
+                const bool in = e < valid && (top == 32 || (key >> top) == prefix);
+                if (in && key == 0) zeros++;
+                else if (in) atomicAdd(&lh[(key >> shift) & (NB - 1)], 1u);
+              }
+            });
+  for (int d = 32; d >= 1; d >>= 1) zeros += __shfl_xor(zeros, d);
+  if ((threadIdx.x & 63) == 0 && zeros) atomicAdd(&lh[0], zeros);
   __syncthreads();
-  if (suf[t] >= need && suf[t + 1] < need) {
-    st->prefix |= (uint32_t)t << shift;
-    st->mask |= 0xFFu << shift;
-    st->need = need - suf[t + 1];
+  for (int i = threadIdx.x; i < NB; i += kTopkThreads) {
+    const uint32_t c = lh[i];
+    if (c) atomicAdd(&hist[i], c);
   }
+}
+
+__global__ __launch_bounds__(kTopkThreads) void topk_count_a_kernel(const float* __restrict__ v, int64_t n,
+                                                                    TopkScratch* sc) {
+  count_keys<kBinsA>(v, n, 32, 0, kShiftA, sc->a);
+}
+
+__global__ __launch_bounds__(kTopkThreads) void topk_count_b_kernel(const float* __restrict__ v, int64_t n, uint32_t k,
+                                                                    TopkScratch* sc) {
+  const Digit a = find_digit<kBinsA>(sc->a, k);
+  count_keys<kBinsB>(v, n, kShiftA, a.d, kShiftB, sc->b);
+}
+
+// Keeps the keys above the prefix, zeroes those below, and keeps and lists the
+// ones that share it.  With too many of those the vector is left to
+// topk_write_kernel.
+__global__ __launch_bounds__(kTopkThreads) void topk_split_kernel(const float* v, int64_t n, uint32_t k,
+                                                                  TopkScratch* sc, float* out) {
+  const Digit p = find_prefix(sc, k);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    sc->prefix = p.d;
+    sc->need = p.need;
+    sc->count = p.count;
+  }
+  if (p.count > kMaxCand) {
+    if (blockIdx.x == 0 && threadIdx.x < kBinsC) sc->c[threadIdx.x] = 0;
+    return;
+  }
+  const int64_t stride = (int64_t)gridDim.x * kTopkTile;
+  for_each4(v, ((int64_t)blockIdx.x * kTopkThreads + threadIdx.x) * 4, stride, n,
+            [&](int64_t i, float4 x, int valid) __attribute__((always_inline)) {
+              float t[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+              for (int e = 0; e < 4; e++) {
+                const uint32_t key = mag_key(t[e]), pre = key >> kShiftB;
+                if (e < valid && pre == p.d)  // larger keys first, then lower indices
+                  sc->cand[atomicAdd(&sc->n_cand, 1u)] =
+                      ((uint64_t)key << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)(i + e));
+                if (pre < p.d) t[e] = 0.0f;
+              }
+              store4(out, i, valid, make_float4(t[0], t[1], t[2], t[3]));
+            });
+}
+
+// Few candidates: a wave per candidate ranks it and zeroes it if it comes
+// after the `need`-th.  Many: the last digit's counts.
+__global__ __launch_bounds__(kTopkThreads) void topk_finish_kernel(const float* v, int64_t n, TopkScratch* sc,
+                                                                   float* out) {
+  const uint32_t need = sc->need, count = sc->count;
+  if (count > kMaxCand) {
+    count_keys<kBinsC>(v, n, kShiftB, sc->prefix, 0, sc->c);
+    return;
+  }
+  if (need == count) return;
+  const int lane = threadIdx.x & 63;
+  const uint32_t waves = gridDim.x * (kTopkThreads / 64);
+  for (uint32_t i = blockIdx.x * (kTopkThreads / 64) + (threadIdx.x >> 6); i < count; i += waves) {
+    const uint64_t mine = sc->cand[i];
+    uint32_t rank = 0;
+    for (uint32_t j = lane; j < count; j += 64) rank += sc->cand[j] > mine ? 1u : 0u;
+    for (int d = 32; d >= 1; d >>= 1) rank += __shfl_xor(rank, d);
+    if (lane == 0 && rank >= need) out[0xFFFFFFFFu - (uint32_t)mine] = 0.0f;
+  }
+}
+
+// The whole threshold key, and how many keys equal to it are kept.
+__device__ inline Digit find_key(const TopkScratch* __restrict__ sc) {
+  const Digit c = find_digit<kBinsC>(sc->c, sc->need);
+  return Digit{(sc->prefix << kShiftB) | c.d, c.need, c.count};
 }
 
 // Per chunk: how many keys equal the threshold.
-__global__ __launch_bounds__(kThreads) void topk_tie_count_kernel(const float* __restrict__ v, int64_t n,
-                                                                  int64_t chunk,
-                                                                  const TopkState* __restrict__ st,
-                                                                  uint32_t* __restrict__ ties) {
-  __shared__ uint32_t wsum[kThreads / 64];
-  const uint32_t T = st->prefix;
+__global__ __launch_bounds__(kTopkThreads) void topk_tie_count_kernel(const float* __restrict__ v, int64_t n,
+                                                                      int64_t chunk, TopkScratch* sc) {
+  __shared__ uint32_t wsum[kTopkThreads / 64];
+  if (sc->count <= kMaxCand) return;
+  const uint32_t T = find_key(sc).d;
   const int64_t c0 = (int64_t)blockIdx.x * chunk;
   const int64_t c1 = c0 + chunk < n ? c0 + chunk : n;
   uint32_t cnt = 0;
-  for (int64_t i = c0 + threadIdx.x * 4; i < c1; i += kTile) {
+  for (int64_t i = c0 + threadIdx.x * 4; i < c1; i += kTopkTile) {
     int valid;
     const float4 x = load4(v, i, c1, valid);
     const float t[4] = {x.x, x.y, x.z, x.w};
@@ -132,30 +269,31 @@ __global__ __launch_bounds__(kThreads) void topk_tie_count_kernel(const float* _
   __syncthreads();
   if (threadIdx.x == 0) {
     uint32_t s = 0;
-    for (int w = 0; w < kThreads / 64; w++) s += wsum[w];
-    ties[blockIdx.x] = s;
+    for (int w = 0; w < kTopkThreads / 64; w++) s += wsum[w];
+    sc->ties[blockIdx.x] = s;
   }
 }
 
 // Ordered pass over one chunk: keep keys above T, and keys equal to T whose
 // rank among equal keys (in index order) is below `need`.
-__global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* v, int64_t n, int64_t chunk,
-                                                              const TopkState* __restrict__ st,
-                                                              const uint32_t* __restrict__ ties,
-                                                              float* out) {
-  __shared__ uint32_t wtot[2][kThreads / 64];
+__global__ __launch_bounds__(kTopkThreads) void topk_write_kernel(const float* v, int64_t n, int64_t chunk,
+                                                                  const TopkScratch* __restrict__ sc, float* out) {
+  constexpr int NW = kTopkThreads / 64;
+  __shared__ uint32_t wtot[2][NW];
   __shared__ uint32_t base_sh;
+  if (sc->count <= kMaxCand) return;
+  const Digit th = find_key(sc);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t T = st->prefix, need = st->need;
+  const uint32_t T = th.d, need = th.need;
   // equal keys in the chunks before this one
   uint32_t before = 0;
-  for (int b = threadIdx.x; b < (int)blockIdx.x; b += kThreads) before += ties[b];
+  for (int b = threadIdx.x; b < (int)blockIdx.x; b += kTopkThreads) before += sc->ties[b];
   for (int d = 32; d >= 1; d >>= 1) before += __shfl_xor(before, d);
   if (lane == 0) wtot[0][wave] = before;
   __syncthreads();
   if (threadIdx.x == 0) {
     uint32_t s = 0;
-    for (int w = 0; w < kThreads / 64; w++) s += wtot[0][w];
+    for (int w = 0; w < NW; w++) s += wtot[0][w];
     base_sh = s;
   }
   __syncthreads();
@@ -163,7 +301,7 @@ __global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* v, in
   const int64_t c0 = (int64_t)blockIdx.x * chunk;
   const int64_t c1 = c0 + chunk < n ? c0 + chunk : n;
   int buf = 1;
-  for (int64_t i0 = c0; i0 < c1; i0 += kTile) {
+  for (int64_t i0 = c0; i0 < c1; i0 += kTopkTile) {
     const int64_t i = i0 + threadIdx.x * 4;
     int valid;
     const float4 x = load4(v, i, c1, valid);
@@ -184,7 +322,7 @@ __global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* v, in
     __syncthreads();
     uint32_t woff = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < kThreads / 64; w++) {
+    for (int w = 0; w < NW; w++) {
       const uint32_t s = wtot[buf][w];
       woff += (w < wave) ? s : 0u;
       tot += s;
@@ -205,6 +343,82 @@ __global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* v, in
   }
 }
 
+// Vectors of at most kSmall values in one block: the values in registers,
+// the three digits' counts in LDS, ties ranked by a block scan per tile.  One
+// launch where the passes above are seven.
+constexpr int kSmallTiles = 8, kSmall = kSmallTiles * kTopkTile;
+__global__ __launch_bounds__(kTopkThreads) void topk_small_kernel(const float* v, int n, uint32_t k, float* out) {
+  constexpr int NW = kTopkThreads / 64;
+  __shared__ uint32_t ha[kBinsA], hb[kBinsB], hc[kBinsC], wtot[2][NW];
+  for (int i = threadIdx.x; i < kBinsA; i += kTopkThreads) ha[i] = 0;
+  for (int i = threadIdx.x; i < kBinsB; i += kTopkThreads) hb[i] = 0;
+  if (threadIdx.x < kBinsC) hc[threadIdx.x] = 0;
+  float x[kSmallTiles][4];
+  int valid[kSmallTiles];
+#pragma unroll
+  for (int u = 0; u < kSmallTiles; u++) {
+    const int64_t i = (int64_t)u * kTopkTile + threadIdx.x * 4;
+    const float4 t = load4(v, i, n, valid[u]);
+    x[u][0] = t.x, x[u][1] = t.y, x[u][2] = t.z, x[u][3] = t.w;
+  }
+  __syncthreads();
+  auto count = [&](uint32_t* h, int top, uint32_t prefix, int shift, int nb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kSmallTiles; u++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const uint32_t key = mag_key(x[u][e]);
+        if (e < valid[u] && (top == 32 || (key >> top) == prefix)) atomicAdd(&h[(key >> shift) & (nb - 1)], 1u);
+      }
+    __syncthreads();
+  };
+  count(ha, 32, 0, kShiftA, kBinsA);
+  const Digit a = find_digit<kBinsA>(ha, k);
+  count(hb, kShiftA, a.d, kShiftB, kBinsB);
+  const Digit b = find_digit<kBinsB>(hb, a.need);
+  const uint32_t pre = (a.d << (kShiftA - kShiftB)) | b.d;
+  count(hc, kShiftB, pre, 0, kBinsC);
+  const Digit c = find_digit<kBinsC>(hc, b.need);
+  const uint32_t T = (pre << kShiftB) | c.d;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t running = 0;
+#pragma unroll
+  for (int u = 0; u < kSmallTiles; u++) {
+    if (u * kTopkTile >= n) break;
+    uint32_t rank = 0;
+    if (c.need < c.count) {  // some of the ties go
+      uint32_t eq = 0;
+#pragma unroll
+      for (int e = 0; e < 4; e++) eq += (e < valid[u] && mag_key(x[u][e]) == T) ? 1u : 0u;
+      uint32_t inc = eq;
+      for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(inc, d);
+        if (lane >= d) inc += y;
+      }
+      if (lane == 63) wtot[u & 1][wave] = inc;
+      __syncthreads();
+      uint32_t woff = 0, tot = 0;
+#pragma unroll
+      for (int w = 0; w < NW; w++) {
+        const uint32_t t = wtot[u & 1][w];
+        woff += w < wave ? t : 0u;
+        tot += t;
+      }
+      rank = running + woff + inc - eq;  // equal keys before this thread's first element
+      running += tot;
+    }
+    float t[4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const uint32_t key = mag_key(x[u][e]);
+      const bool keep = key > T || (key == T && rank < c.need);
+      if (key == T) rank++;
+      t[e] = keep ? x[u][e] : 0.0f;
+    }
+    store4(out, (int64_t)u * kTopkTile + threadIdx.x * 4, valid[u], make_float4(t[0], t[1], t[2], t[3]));
+  }
+}
+
 __global__ void fill_zero_kernel(float* __restrict__ out, int64_t n) {
   const int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
   if (i < n) {
@@ -219,20 +433,18 @@ __global__ __launch_bounds__(kThreads) void minmax_kernel(const float* __restric
   __shared__ LossyMinMax ws[kThreads / 64];
   float mn = INFINITY, mx = -INFINITY;
   uint32_t bad = 0;
-  const int64_t stride = (int64_t)gridDim.x * kThreads * 4;
-  for (int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4; i < n; i += stride) {
-    int valid;
-    const float4 x = load4(v, i, n, valid);
-    const float t[4] = {x.x, x.y, x.z, x.w};
+  for_each4(v, ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4, (int64_t)gridDim.x * kTile, n,
+            [&](int64_t, float4 x, int valid) __attribute__((always_inline)) {
+              const float t[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-    for (int e = 0; e < 4; e++) {
-      if (e < valid) {
-        bad += isfinite(t[e]) ? 0u : 1u;
-        mn = fminf(mn, t[e]);
-        mx = fmaxf(mx, t[e]);
-      }
-    }
-  }
+              for (int e = 0; e < 4; e++) {
+                if (e < valid) {
+                  bad += isfinite(t[e]) ? 0u : 1u;
+                  mn = fminf(mn, t[e]);
+                  mx = fmaxf(mx, t[e]);
+                }
+              }
+            });
   for (int d = 32; d >= 1; d >>= 1) {
     mn = fminf(mn, __shfl_xor(mn, d));
     mx = fmaxf(mx, __shfl_xor(mx, d));
@@ -251,8 +463,22 @@ __global__ __launch_bounds__(kThreads) void minmax_kernel(const float* __restric
   }
 }
 
-__global__ __launch_bounds__(kThreads) void minmax_final_kernel(const LossyMinMax* __restrict__ part, int nparts,
-                                                                LossyMinMax* __restrict__ res) {
+// Eq. 4 in float32: one rounding per operation, no contraction, round half
+// to even.  span = max - min > 0; every index lands in [0, levels].
+__device__ inline uint32_t eq4_index(float x, float mn, float span, float levels) {
+#pragma clang fp contract(off)
+  const float t = (x - mn) / span;
+  return (uint32_t)__builtin_rintf(t * levels);
+}
+
+// Every block merges the min/max partials itself (at most 16 KB from L2; a
+// launch of its own took 3 us and a gap); block 0 leaves the result in res for
+// the host.  Nothing is written for a vector with NaN or infinite values.
+template <typename IdxT>
+__global__ __launch_bounds__(kThreads) void quantize_kernel(const float* __restrict__ v, int64_t n,
+                                                            const LossyMinMax* __restrict__ part, int nparts,
+                                                            LossyMinMax* __restrict__ res, float levels,
+                                                            IdxT* __restrict__ idx) {
   __shared__ LossyMinMax ws[kThreads / 64];
   float mn = INFINITY, mx = -INFINITY;
   uint32_t bad = 0;
@@ -268,46 +494,33 @@ __global__ __launch_bounds__(kThreads) void minmax_final_kernel(const LossyMinMa
   }
   if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = LossyMinMax{mn, mx, bad, 0u};
   __syncthreads();
-  if (threadIdx.x == 0) {
-    LossyMinMax r = ws[0];
-    for (int w = 1; w < kThreads / 64; w++) {
-      r.mn = fminf(r.mn, ws[w].mn);
-      r.mx = fmaxf(r.mx, ws[w].mx);
-      r.nonfinite += ws[w].nonfinite;
-    }
-    *res = r;
+  LossyMinMax r = ws[0];
+  for (int w = 1; w < kThreads / 64; w++) {
+    r.mn = fminf(r.mn, ws[w].mn);
+    r.mx = fmaxf(r.mx, ws[w].mx);
+    r.nonfinite += ws[w].nonfinite;
   }
-}
-
-// Eq. 4 in float32: one rounding per operation, no contraction, round half
-// to even.  span = max - min > 0; every index lands in [0, levels].
-__device__ inline uint32_t eq4_index(float x, float mn, float span, float levels) {
-#pragma clang fp contract(off)
-  const float t = (x - mn) / span;
-  return (uint32_t)__builtin_rintf(t * levels);
-}
-
-template <typename IdxT>
-__global__ __launch_bounds__(kThreads) void quantize_kernel(const float* __restrict__ v, int64_t n, float mn,
-                                                            float mx, float levels, IdxT* __restrict__ idx) {
-  const int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
-  if (i >= n) return;
-  int valid;
-  const float4 x = load4(v, i, n, valid);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *res = r;
+  if (r.nonfinite) return;
+  mn = r.mn;
+  mx = r.mx;
   const float span = mx - mn;
-  const float t[4] = {x.x, x.y, x.z, x.w};
-  uint32_t q[4];
+  for_each4(v, ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4, (int64_t)gridDim.x * kTile, n,
+            [&](int64_t i, float4 x, int valid) __attribute__((always_inline)) {
+              const float t[4] = {x.x, x.y, x.z, x.w};
+              uint32_t q[4];
 #pragma unroll
-  for (int e = 0; e < 4; e++) q[e] = mx > mn ? eq4_index(t[e], mn, span, levels) : 0u;
-  if (valid == 4) {
-    if constexpr (sizeof(IdxT) == 1) {
-      *reinterpret_cast<uint32_t*>(idx + i) = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24);
-    } else {
-      *reinterpret_cast<uint2*>(idx + i) = make_uint2(q[0] | (q[1] << 16), q[2] | (q[3] << 16));
-    }
-  } else {
-    for (int e = 0; e < valid; e++) idx[i + e] = (IdxT)q[e];
-  }
+              for (int e = 0; e < 4; e++) q[e] = mx > mn ? eq4_index(t[e], mn, span, levels) : 0u;
+              if (valid == 4) {
+                if constexpr (sizeof(IdxT) == 1) {
+                  *reinterpret_cast<uint32_t*>(idx + i) = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24);
+                } else {
+                  *reinterpret_cast<uint2*>(idx + i) = make_uint2(q[0] | (q[1] << 16), q[2] | (q[3] << 16));
+                }
+              } else {
+                for (int e = 0; e < valid; e++) idx[i + e] = (IdxT)q[e];
+              }
+            });
 }
 
 // ------------------------------------------------------------------- signs
@@ -335,16 +548,17 @@ inline unsigned blocks_for(int64_t n, int64_t per_block) { return (unsigned)((n 
 }  // namespace
 
 // ------------------------------------------------------------- launchers
-size_t lossy_workspace_bytes() {
-  return sizeof(TopkState) + 256 * sizeof(uint32_t) + kMaxChunks * sizeof(uint32_t) +
-         (kGridStride + 1) * sizeof(LossyMinMax);
-}
+// Top-k and min/max calls use the same bytes (one call at a time on a
+// workspace): the top-k scratch, or the min/max partials and their result.
+constexpr size_t kLossyBytes = std::max(sizeof(TopkScratch), (kGridStride + 1) * sizeof(LossyMinMax));
+static_assert(kLossyBytes <= 32768, "the library-owned scratch holds it");
+size_t lossy_workspace_bytes() { return kLossyBytes; }
 
 int64_t topk_chunk(int64_t n) {
   // a multiple of the tile, so that only the vector's last float4 can be partial
   const int64_t per = (n + kMaxChunks - 1) / kMaxChunks;
-  const int64_t c = (per + kTile - 1) / kTile * kTile;
-  return c > kTile ? c : kTile;
+  const int64_t c = (per + kTopkTile - 1) / kTopkTile * kTopkTile;
+  return c > kTopkTile ? c : kTopkTile;
 }
 
 hipError_t launch_sparsify_topk(const float* v, int64_t n, int64_t k, float* out, void* ws, hipStream_t s) {
@@ -354,32 +568,26 @@ hipError_t launch_sparsify_topk(const float* v, int64_t n, int64_t k, float* out
     return hipGetLastError();
   }
   if (k > n) k = n;
-  uint8_t* w = (uint8_t*)ws;
-  TopkState* st = (TopkState*)w;
-  uint32_t* hist = (uint32_t*)(w + sizeof(TopkState));
-  uint32_t* ties = hist + 256;
-  hipLaunchKernelGGL(topk_init_kernel, dim3(1), dim3(256), 0, s, st, hist, (uint32_t)k);
-  const unsigned g = std::min<unsigned>(kGridStride, blocks_for(n, kTile));
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    hipLaunchKernelGGL(topk_hist_kernel, dim3(g), dim3(kThreads), 0, s, v, n, (const TopkState*)st, hist,
-                       shift);
-    hipLaunchKernelGGL(topk_select_kernel, dim3(1), dim3(kThreads), 0, s, st, hist, shift);
+  const uint32_t kk = (uint32_t)k;
+  if (n <= kSmall) {
+    hipLaunchKernelGGL(topk_small_kernel, dim3(1), dim3(kTopkThreads), 0, s, v, (int)n, kk, out);
+    return hipGetLastError();
   }
+  TopkScratch* sc = (TopkScratch*)ws;
+  // one block per CU while the vector comes from the caches (each block also
+  // adds its counts to the global ones), two beyond
+  const unsigned most = n <= (32 << 20) ? 256 : 512;
+  const dim3 g(std::min(most, blocks_for(n, kTopkTile))), block(kTopkThreads);
+  hipLaunchKernelGGL(topk_init_kernel, dim3(1), block, 0, s, sc);
+  hipLaunchKernelGGL(topk_count_a_kernel, g, block, 0, s, v, n, sc);
+  hipLaunchKernelGGL(topk_count_b_kernel, g, block, 0, s, v, n, kk, sc);
+  hipLaunchKernelGGL(topk_split_kernel, g, block, 0, s, v, n, kk, sc, out);
+  hipLaunchKernelGGL(topk_finish_kernel, g, block, 0, s, v, n, sc, out);
+  // these two return at once unless the candidates were too many
   const int64_t chunk = topk_chunk(n);
-  const unsigned nchunks = blocks_for(n, chunk);
-  hipLaunchKernelGGL(topk_tie_count_kernel, dim3(nchunks), dim3(kThreads), 0, s, v, n, chunk,
-                     (const TopkState*)st, ties);
-  hipLaunchKernelGGL(topk_write_kernel, dim3(nchunks), dim3(kThreads), 0, s, v, n, chunk, (const TopkState*)st,
-                     (const uint32_t*)ties, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_minmax(const float* v, int64_t n, void* ws, LossyMinMax* res, hipStream_t s) {
-  uint8_t* w = (uint8_t*)ws + sizeof(TopkState) + 256 * sizeof(uint32_t) + kMaxChunks * sizeof(uint32_t);
-  LossyMinMax* part = (LossyMinMax*)w;
-  const unsigned g = std::max(1u, std::min<unsigned>(kGridStride, blocks_for(n, kTile)));
-  hipLaunchKernelGGL(minmax_kernel, dim3(g), dim3(kThreads), 0, s, v, n, part);
-  hipLaunchKernelGGL(minmax_final_kernel, dim3(1), dim3(kThreads), 0, s, (const LossyMinMax*)part, (int)g, res);
+  const dim3 nchunks(blocks_for(n, chunk));
+  hipLaunchKernelGGL(topk_tie_count_kernel, nchunks, block, 0, s, v, n, chunk, sc);
+  hipLaunchKernelGGL(topk_write_kernel, nchunks, block, 0, s, v, n, chunk, (const TopkScratch*)sc, out);
   return hipGetLastError();
 }
 
@@ -417,21 +625,21 @@ hipError_t lossy_scratch(void** ptr, size_t* bytes) {
   return hipSuccess;
 }
 
-LossyMinMax* lossy_minmax_slot(void* ws) {
-  return (LossyMinMax*)((uint8_t*)ws + sizeof(TopkState) + 256 * sizeof(uint32_t) +
-                        kMaxChunks * sizeof(uint32_t) + kGridStride * sizeof(LossyMinMax));
-}
+LossyMinMax* lossy_minmax_slot(void* ws) { return (LossyMinMax*)ws + kGridStride; }
 
-hipError_t launch_quantize_linear(const float* v, int64_t n, int bits, float mn, float mx, void* idx,
-                                  hipStream_t s) {
+hipError_t launch_quantize_linear(const float* v, int64_t n, int bits, void* idx, void* ws, hipStream_t s) {
   if (n == 0) return hipSuccess;
+  LossyMinMax* part = (LossyMinMax*)ws;
+  const unsigned g = std::min<unsigned>(kGridStride, blocks_for(n, kTile));
+  hipLaunchKernelGGL(minmax_kernel, dim3(g), dim3(kThreads), 0, s, v, n, part);
   const float levels = (float)((1u << bits) - 1u);
+  const dim3 grid(std::min<unsigned>(2048, blocks_for(n, kTile))), block(kThreads);
   if (bits <= 8)
-    hipLaunchKernelGGL(quantize_kernel<uint8_t>, dim3(blocks_for(n, kTile)), dim3(kThreads), 0, s, v, n, mn, mx,
-                       levels, (uint8_t*)idx);
+    hipLaunchKernelGGL(quantize_kernel<uint8_t>, grid, block, 0, s, v, n, (const LossyMinMax*)part, (int)g,
+                       lossy_minmax_slot(ws), levels, (uint8_t*)idx);
   else
-    hipLaunchKernelGGL(quantize_kernel<uint16_t>, dim3(blocks_for(n, kTile)), dim3(kThreads), 0, s, v, n, mn, mx,
-                       levels, (uint16_t*)idx);
+    hipLaunchKernelGGL(quantize_kernel<uint16_t>, grid, block, 0, s, v, n, (const LossyMinMax*)part, (int)g,
+                       lossy_minmax_slot(ws), levels, (uint16_t*)idx);
   return hipGetLastError();
 }
 

@@ -1,0 +1,47 @@
+"""Top-k against the oracle where its routes meet: the one-block kernel and the
+passes, and around the number of keys the candidate list holds (keys that
+share the threshold's leading 23 bits)."""
+import numpy as np
+import pytest
+
+from gpu_util import log
+from oracle import lossy as olossy
+from paper_2409_17836_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(v, ks):
+    import torch
+    dv = torch.from_numpy(v).cuda()
+    for k in ks:
+        got = B.sparsify_topk(dv, k).cpu().numpy()
+        assert got.tobytes() == olossy.sparsify_topk(v, k).tobytes(), (v.size, k)
+
+
+@pytest.mark.parametrize("n", [4096, 4097, 32764, 32768, 32769, 36000, 200001])
+def test_routes_by_size(n):
+    log(f"top-k routes n={n}")
+    rng = np.random.default_rng(n)
+    v = rng.normal(0, 1e-3, n).astype(np.float32)
+    _check(v, [1, n // 10, n // 2, n - 1, n])
+    v[rng.random(n) < 0.7] = 0.0                     # the threshold is zero for large k
+    _check(v, [n // 10, n // 2])
+    _check(np.full(n, -2.5, np.float32), [1, n // 3, n])
+
+
+@pytest.mark.parametrize("same", [1, 999, 1000, 1001, 5000])
+def test_candidates_around_the_list(same):
+    """`same` keys share their leading 23 bits: equal ones in one half (ties by
+    index), ones that differ in the last 8 bits in the other."""
+    n = 100003
+    log(f"top-k candidates {same}")
+    rng = np.random.default_rng(same)
+    v = rng.normal(0, 1e-3, n).astype(np.float32)
+    v[np.abs(np.abs(v) - 5e-4) < 1e-6] = 0.0
+    bits = np.full(same, np.float32(5e-4).view(np.uint32) & 0xFFFFFF00, np.uint32)
+    bits[: same // 2] |= rng.integers(0, 256, same // 2).astype(np.uint32)
+    at = rng.choice(n, same, replace=False)
+    v[at] = bits.view(np.float32) * rng.choice(np.array([-1, 1], np.float32), same)
+    above = int((np.abs(v) > 5.001e-4).sum())
+    _check(v, sorted({above + 1, above + same // 4 + 1, above + (3 * same) // 4 + 1, above + same}))
