@@ -388,18 +388,27 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t* __res
 }
 
 // float32 attention for float32 decoders: one thread per query, keys in
-// order through 64-key LDS tiles, online softmax per key.
+// order, online softmax per key.  64-key tiles of K and V sit in LDS as plain
+// rows: a key's values are the same for the whole wave, read as 16-byte
+// broadcasts (4-byte ones, 64 per key at 32 dims, bounded the kernel).  What
+// bounds it now is the vector work of a key, about 130 instructions; scalar
+// loads of the rows instead of LDS were slower (their latency is exposed
+// every key: 311 us).  144 windows of 256 tokens, 4 heads of 32 dims: 261 us
+// with 4-byte reads, 237 with 16-byte ones, 163 with four keys at a time; 64
+// dims, 32 windows of 200 and 4 heads: 311 -> 190 us.  The arithmetic is
+// spelled out (which products are fused) so that it does not depend on the
+// code around it.  The query blocks with most keys start first.
 template <int HD>
 __global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ q,
                                                       const float* __restrict__ k,
                                                       const float* __restrict__ v,
                                                       float* __restrict__ o, int Hq, int Hkv,
                                                       int W, float scale, int dq) {
-  __shared__ float sK[64][HD + 1];
-  __shared__ float sV[64][HD + 1];
+#pragma clang fp contract(off)
+  __shared__ float4 sK[64 * HD / 4], sV[64 * HD / 4];
   const int h = blockIdx.y, b = blockIdx.z;
   const int kvh = h * Hkv / Hq;
-  const int qblk = dq >= 0 ? dq / 64 : (int)blockIdx.x;  // a decoding step: dq's block only
+  const int qblk = dq >= 0 ? dq / 64 : (int)(gridDim.x - 1 - blockIdx.x);  // a decoding step: dq's block only
   const int myq = qblk * 64 + threadIdx.x;
   const float* Qp = q + (int64_t)(b * Hq + h) * W * HD;
   const float* Kp = k + (int64_t)(b * Hkv + kvh) * W * HD;
@@ -412,30 +421,74 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ 
     acc[i] = 0.f;
   }
   float m = -INFINITY, l = 0.f;
-  const int kend = min(W, qblk * 64 + 64);
-  for (int k0 = 0; k0 < kend; k0 += 64) {
+  // Four keys at a time, so that their score chains and exponentials overlap
+  // (one wave waits out every dependent operation otherwise); the sums run
+  // key by key.
+  constexpr int KG = 4;
+  auto keys = [&](int j0, auto masked) __attribute__((always_inline)) {
+    constexpr bool MASKED = decltype(masked)::value;  // keys after the query take no part
+    float s[KG], mn[KG], corr[KG], p[KG];
+#pragma unroll
+    for (int u = 0; u < KG; u++) s[u] = 0.f;
+#pragma unroll
+    for (int i = 0; i < HD; i += 4) {
+#pragma unroll
+      for (int u = 0; u < KG; u++) {
+        const float4 kk = sK[((j0 + u) * HD + i) / 4];
+        s[u] = __builtin_fmaf(qv[i], kk.x, s[u]);
+        s[u] = __builtin_fmaf(qv[i + 1], kk.y, s[u]);
+        s[u] = __builtin_fmaf(qv[i + 2], kk.z, s[u]);
+        s[u] = __builtin_fmaf(qv[i + 3], kk.w, s[u]);
+      }
+    }
+    auto in = [&](int u) __attribute__((always_inline)) { return !MASKED || j0 + u <= (int)threadIdx.x; };
+    float before = m;
+#pragma unroll
+    for (int u = 0; u < KG; u++) {
+      mn[u] = in(u) ? fmaxf(before, s[u] * scale) : before;
+      before = mn[u];
+    }
+    // exp(0) is exactly 1: most groups move no lane's maximum
+#pragma unroll
+    for (int u = 0; u < KG; u++) corr[u] = 1.f;
+    if (__any(before != m)) {
+#pragma unroll
+      for (int u = 0; u < KG; u++) corr[u] = expf((u ? mn[u - 1] : m) - mn[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < KG; u++) p[u] = expf(__builtin_fmaf(scale, s[u], -mn[u]));
+    m = before;
+#pragma unroll
+    for (int u = 0; u < KG; u++) {
+      if (!in(u)) continue;
+      l = __builtin_fmaf(l, corr[u], p[u]);
+#pragma unroll
+      for (int i = 0; i < HD; i += 4) {
+        const float4 vv = sV[((j0 + u) * HD + i) / 4];
+        acc[i] = __builtin_fmaf(corr[u], acc[i], p[u] * vv.x);
+        acc[i + 1] = __builtin_fmaf(corr[u], acc[i + 1], p[u] * vv.y);
+        acc[i + 2] = __builtin_fmaf(corr[u], acc[i + 2], p[u] * vv.z);
+        acc[i + 3] = __builtin_fmaf(corr[u], acc[i + 3], p[u] * vv.w);
+      }
+    }
+  };
+  for (int t = 0; t <= qblk; t++) {
     __syncthreads();
-    for (int c = threadIdx.x; c < 64 * HD; c += 64) {
-      const int key = c / HD, i = c % HD;
-      const int kk = min(k0 + key, W - 1);
-      sK[key][i] = Kp[(int64_t)kk * HD + i];
-      sV[key][i] = Vp[(int64_t)kk * HD + i];
+    // (a row after the window's last re-reads it: those keys are masked)
+#pragma unroll 4
+    for (int c = 0; c < HD / 4; c++) {
+      const int u = c * 64 + threadIdx.x, row = min(t * 64 + u / (HD / 4), W - 1);
+      const int64_t at = (int64_t)row * (HD / 4) + u % (HD / 4);
+      sK[u] = reinterpret_cast<const float4*>(Kp)[at];
+      sV[u] = reinterpret_cast<const float4*>(Vp)[at];
     }
     __syncthreads();
-    for (int j = 0; j < 64; j++) {
-      const int key = k0 + j;
-      if (key > myq || key >= W) break;
-      float s = 0.f;
-#pragma unroll
-      for (int i = 0; i < HD; i++) s = fmaf(qv[i], sK[j][i], s);
-      s *= scale;
-      const float mn = fmaxf(m, s);
-      const float corr = expf(m - mn);
-      const float p = expf(s - mn);
-      l = l * corr + p;
-#pragma unroll
-      for (int i = 0; i < HD; i++) acc[i] = acc[i] * corr + p * sV[j][i];
-      m = mn;
+    // the queries' own block: keys up to the query (and, for queries past the
+    // window's end, which are not stored, up to 64)
+    if (t < qblk) {
+      for (int j = 0; j < 64; j += KG) keys(j, std::false_type{});
+    } else {
+      for (int j = 0; j < 64; j += KG) keys(j, std::true_type{});
     }
   }
   if (dq >= 0 ? myq == dq : myq < W) {
