@@ -25,7 +25,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0          # MI355X dense bf16 matrix peak
-PEAK_F32_VECTOR_TFLOPS = 157.3     # MI355X float32 vector peak (the tiny model's FMA kernels)
+PEAK_F32_TFLOPS = 157.3            # MI355X float32 peak, matrix or (packed) vector
 HBM_PEAK_GBS = 8000.0              # MI355X HBM3E bandwidth (the decoding step is bound by it)
 DOMINANT = "gemm_up"               # gate/up projection + SwiGLU: 44% of the FLOPs
 
@@ -115,8 +115,8 @@ def cpu_baseline(w, host_weights, raw_values, all_positions=256, one_positions=3
 
 # Sources of the dominant kernel: a stored traffic figure is used only while
 # they are unchanged since its counters were taken.
-KERNEL_SOURCES = ("paper_2409_17836_amd/csrc/gemm_bf16.hip", "paper_2409_17836_amd/csrc/epilogue.h",
-                  "paper_2409_17836_amd/csrc/common.h")
+KERNEL_SOURCES = ("paper_2409_17836_amd/csrc/gemm_bf16.hip", "paper_2409_17836_amd/csrc/gemm_tile.h",
+                  "paper_2409_17836_amd/csrc/epilogue.h", "paper_2409_17836_amd/csrc/common.h")
 
 
 def kernel_source_hash():
@@ -358,7 +358,7 @@ def main():
     ms_step = dt * 1e3 / args.steps
 
     f32 = w.model.dtype == "f32"
-    peak = PEAK_F32_VECTOR_TFLOPS if f32 else PEAK_BF16_TFLOPS
+    peak = PEAK_F32_TFLOPS if f32 else PEAK_BF16_TFLOPS
     flops_step = {k: model.flops(Bw, W, k) for k in B.KINDS}
     total_flops = sum(flops_step.values())
     mfma_util = None if f32 else total_flops * args.steps / dt / (PEAK_BF16_TFLOPS * 1e12)
@@ -413,7 +413,7 @@ def main():
             "kernel": f"{DOMINANT} ({'fc' if w.model.arch == 'gpt2' else 'gate/up'} projection "
                       f"{Bw * W}x{(1 if w.model.arch == 'gpt2' else 2) * w.model.d_ff}x{w.model.d_model} "
                       f"with fused {'GELU' if w.model.arch == 'gpt2' else 'SwiGLU'}"
-                      + (", float32 FMA kernel" if f32 else "") + ")",
+                      + (", float32 MFMA kernel" if f32 else "") + ")",
             "bound": "alu" if f32 else "mfma",
             "achieved": round(achieved, 2),
             "peak": peak,
