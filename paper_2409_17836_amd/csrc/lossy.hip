@@ -212,9 +212,10 @@ __global__ __launch_bounds__(kTopkThreads) void topk_split_kernel(const float* v
 #pragma unroll
               for (int e = 0; e < 4; e++) {
                 const uint32_t key = mag_key(t[e]), pre = key >> kShiftB;
-                if (e < valid && pre == p.d)  // larger keys first, then lower indices
-                  sc->cand[atomicAdd(&sc->n_cand, 1u)] =
-                      ((uint64_t)key << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)(i + e));
+                if (e < valid && pre == p.d) {  // larger keys first, then lower indices
+                  const uint32_t at = atomicAdd(&sc->n_cand, 1u);
+                  if (at < kMaxCand) sc->cand[at] = ((uint64_t)key << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)(i + e));
+                }
                 if (pre < p.d) t[e] = 0.0f;
               }
               store4(out, i, valid, make_float4(t[0], t[1], t[2], t[3]));
@@ -223,6 +224,9 @@ __global__ __launch_bounds__(kTopkThreads) void topk_split_kernel(const float* v
 
 // Few candidates: a wave per candidate ranks it and zeroes it if it comes
 // after the `need`-th.  Many: the last digit's counts.
+// (Overlapping calls on one scratch find each other's list and its length; the
+// checks of the slot above and of the index here keep them in bounds, with
+// wrong values and no more.)
 __global__ __launch_bounds__(kTopkThreads) void topk_finish_kernel(const float* v, int64_t n, TopkScratch* sc,
                                                                    float* out) {
   const uint32_t need = sc->need, count = sc->count;
@@ -238,7 +242,8 @@ __global__ __launch_bounds__(kTopkThreads) void topk_finish_kernel(const float* 
     uint32_t rank = 0;
     for (uint32_t j = lane; j < count; j += 64) rank += sc->cand[j] > mine ? 1u : 0u;
     for (int d = 32; d >= 1; d >>= 1) rank += __shfl_xor(rank, d);
-    if (lane == 0 && rank >= need) out[0xFFFFFFFFu - (uint32_t)mine] = 0.0f;
+    const uint32_t at = 0xFFFFFFFFu - (uint32_t)mine;
+    if (lane == 0 && rank >= need && at < n) out[at] = 0.0f;
   }
 }
 
