@@ -156,7 +156,9 @@ int lmgc_deserialize(const uint8_t* sym, int64_t n_tokens, int64_t n_values,
 int64_t lmgc_keep_count(int64_t n_values, int32_t percent);
 
 /* Device workspace bytes of lmgc_sparsify_topk and lmgc_quantize_linear
- * (a few tens of KiB, independent of n_values), or < 0 if n_values is bad. */
+ * (a few tens of KiB, independent of n_values), or < 0 if n_values is bad.
+ * Workspaces of at least 25632 bytes are taken too: results are the same, and
+ * vectors of more than some 9 million values take more passes. */
 int64_t lmgc_lossy_workspace(int64_t n_values);
 
 /*

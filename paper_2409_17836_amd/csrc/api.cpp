@@ -970,7 +970,7 @@ static int check_lossy_vec(const float* d_values, int64_t n_values, const void* 
 }
 
 static int check_lossy_ws(const void* ws, size_t bytes) {
-  if (!ws || bytes < lossy_workspace_bytes())
+  if (!ws || bytes < lossy_min_workspace_bytes())
     return set_error(LMGC_ESIZE, "lossy workspace needs %zu bytes", lossy_workspace_bytes());
   if ((uintptr_t)ws & 15) return set_error(LMGC_EINVAL, "workspace must be 16-byte aligned");
   return LMGC_OK;
@@ -1006,7 +1006,7 @@ int lmgc_sparsify_topk(const float* d_values, int64_t n_values, int64_t k, float
   if (rc) return rc;
   if (n_values == 0) return LMGC_OK;
   if (k > 0 && (rc = check_lossy_ws(d_workspace, workspace_bytes))) return rc;
-  hipError_t e = launch_sparsify_topk(d_values, n_values, k, d_out, d_workspace, (hipStream_t)stream);
+  hipError_t e = launch_sparsify_topk(d_values, n_values, k, d_out, d_workspace, workspace_bytes, (hipStream_t)stream);
   if (e != hipSuccess) return set_error(LMGC_EDEVICE, "sparsify launch: %s", hipGetErrorString(e));
   return LMGC_OK;
 }
@@ -1023,7 +1023,7 @@ int lmgc_sparsify_topk_noalloc(const float* d_values, int64_t n_values, int64_t 
   if (lossy_workspace_bytes() > cap)
     return set_error(LMGC_ESIZE, "top-k needs %zu bytes of scratch, the library holds %zu", lossy_workspace_bytes(),
                      cap);
-  e = launch_sparsify_topk(d_values, n_values, k, d_out, ws, (hipStream_t)stream);
+  e = launch_sparsify_topk(d_values, n_values, k, d_out, ws, cap, (hipStream_t)stream);
   if (e != hipSuccess) return set_error(LMGC_EDEVICE, "sparsify launch: %s", hipGetErrorString(e));
   return LMGC_OK;
 }

@@ -152,8 +152,12 @@ struct LossyMinMax {
   uint32_t nonfinite;  // values that are NaN or infinite
   uint32_t pad;
 };
+// lossy_workspace_bytes() is what a call makes full use of,
+// lossy_min_workspace_bytes() what it needs.
 size_t lossy_workspace_bytes();
-hipError_t launch_sparsify_topk(const float* v, int64_t n, int64_t k, float* out, void* ws, hipStream_t s);
+size_t lossy_min_workspace_bytes();
+hipError_t launch_sparsify_topk(const float* v, int64_t n, int64_t k, float* out, void* ws, size_t ws_bytes,
+                                hipStream_t s);
 LossyMinMax* lossy_minmax_slot(void* ws);
 // Address (on the current device) and size of the library-owned device
 // scratch that lmgc_sparsify_topk_noalloc uses in place of a workspace.

@@ -31,23 +31,23 @@ constexpr int kTopkThreads = 1024, kTopkTile = kTopkThreads * 4;
 constexpr int kBinsA = 4096, kBinsB = 2048, kBinsC = 256;
 constexpr int kShiftA = 19, kShiftB = 8;
 constexpr int kMaxChunks = 1024;        // ordered chunks of the tie passes
-constexpr int kMaxCand = 1000;          // keys that share the 23-bit prefix
+constexpr uint32_t kMaxCand = 1000;     // keys that share the 23-bit prefix
 
-// Scratch of a top-k call.  A and B are counted by the first two passes; the
-// candidate list and, with too many candidates, the last digit's counts and
-// the chunks' ties share the rest.
+// Scratch of a top-k call.  A and B are counted by the first two passes.  The
+// candidate list takes what the workspace has left (`cap` entries, kMaxCand at
+// most); with more candidates than that the last digit's counts take its place
+// and the chunks' ties that of A.
 struct TopkScratch {
-  uint32_t a[kBinsA];
+  union {
+    uint32_t a[kBinsA];
+    uint32_t ties[kMaxChunks];
+  };
   uint32_t b[kBinsB];
   uint32_t n_cand;
   uint32_t prefix, need, count;  // of topk_split_kernel, for the kernels after it
-  uint32_t pad[12];
   union {
     uint64_t cand[kMaxCand];
-    struct {
-      uint32_t c[kBinsC];
-      uint32_t ties[kMaxChunks];
-    };
+    uint32_t c[kBinsC];
   };
 };
 
@@ -194,14 +194,14 @@ __global__ __launch_bounds__(kTopkThreads) void topk_count_b_kernel(const float*
 // ones that share it.  With too many of those the vector is left to
 // topk_write_kernel.
 __global__ __launch_bounds__(kTopkThreads) void topk_split_kernel(const float* v, int64_t n, uint32_t k,
-                                                                  TopkScratch* sc, float* out) {
+                                                                  uint32_t cap, TopkScratch* sc, float* out) {
   const Digit p = find_prefix(sc, k);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     sc->prefix = p.d;
     sc->need = p.need;
     sc->count = p.count;
   }
-  if (p.count > kMaxCand) {
+  if (p.count > cap) {
     if (blockIdx.x == 0 && threadIdx.x < kBinsC) sc->c[threadIdx.x] = 0;
     return;
   }
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_split_kernel(const float* v
                 const uint32_t key = mag_key(t[e]), pre = key >> kShiftB;
                 if (e < valid && pre == p.d) {  // larger keys first, then lower indices
                   const uint32_t at = atomicAdd(&sc->n_cand, 1u);
-                  if (at < kMaxCand) sc->cand[at] = ((uint64_t)key << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)(i + e));
+                  if (at < cap) sc->cand[at] = ((uint64_t)key << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)(i + e));
                 }
                 if (pre < p.d) t[e] = 0.0f;
               }
@@ -227,10 +227,10 @@ __global__ __launch_bounds__(kTopkThreads) void topk_split_kernel(const float* v
 // (Overlapping calls on one scratch find each other's list and its length; the
 // checks of the slot above and of the index here keep them in bounds, with
 // wrong values and no more.)
-__global__ __launch_bounds__(kTopkThreads) void topk_finish_kernel(const float* v, int64_t n, TopkScratch* sc,
-                                                                   float* out) {
+__global__ __launch_bounds__(kTopkThreads) void topk_finish_kernel(const float* v, int64_t n, uint32_t cap,
+                                                                   TopkScratch* sc, float* out) {
   const uint32_t need = sc->need, count = sc->count;
-  if (count > kMaxCand) {
+  if (count > cap) {
     count_keys<kBinsC>(v, n, kShiftB, sc->prefix, 0, sc->c);
     return;
   }
@@ -255,9 +255,9 @@ __device__ inline Digit find_key(const TopkScratch* __restrict__ sc) {
 
 // Per chunk: how many keys equal the threshold.
 __global__ __launch_bounds__(kTopkThreads) void topk_tie_count_kernel(const float* __restrict__ v, int64_t n,
-                                                                      int64_t chunk, TopkScratch* sc) {
+                                                                      int64_t chunk, uint32_t cap, TopkScratch* sc) {
   __shared__ uint32_t wsum[kTopkThreads / 64];
-  if (sc->count <= kMaxCand) return;
+  if (sc->count <= cap) return;
   const uint32_t T = find_key(sc).d;
   const int64_t c0 = (int64_t)blockIdx.x * chunk;
   const int64_t c1 = c0 + chunk < n ? c0 + chunk : n;
@@ -281,12 +281,12 @@ __global__ __launch_bounds__(kTopkThreads) void topk_tie_count_kernel(const floa
 
 // Ordered pass over one chunk: keep keys above T, and keys equal to T whose
 // rank among equal keys (in index order) is below `need`.
-__global__ __launch_bounds__(kTopkThreads) void topk_write_kernel(const float* v, int64_t n, int64_t chunk,
+__global__ __launch_bounds__(kTopkThreads) void topk_write_kernel(const float* v, int64_t n, int64_t chunk, uint32_t cap,
                                                                   const TopkScratch* __restrict__ sc, float* out) {
   constexpr int NW = kTopkThreads / 64;
   __shared__ uint32_t wtot[2][NW];
   __shared__ uint32_t base_sh;
-  if (sc->count <= kMaxCand) return;
+  if (sc->count <= cap) return;
   const Digit th = find_key(sc);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t T = th.d, need = th.need;
@@ -555,9 +555,17 @@ inline unsigned blocks_for(int64_t n, int64_t per_block) { return (unsigned)((n 
 // ------------------------------------------------------------- launchers
 // Top-k and min/max calls use the same bytes (one call at a time on a
 // workspace): the top-k scratch, or the min/max partials and their result.
+// Smaller workspaces are taken down to kLossyMinBytes, what earlier versions
+// asked for: the candidate list is shorter in them (130 entries, enough for 9
+// million normal values; beyond, the passes for many candidates run).
 constexpr size_t kLossyBytes = std::max(sizeof(TopkScratch), (kGridStride + 1) * sizeof(LossyMinMax));
+constexpr size_t kLossyMinBytes = 25632;
 static_assert(kLossyBytes <= 32768, "the library-owned scratch holds it");
+static_assert(offsetof(TopkScratch, c) + sizeof(TopkScratch::c) <= kLossyMinBytes &&
+                  (kGridStride + 1) * sizeof(LossyMinMax) <= kLossyMinBytes,
+              "the smallest workspace holds everything but the whole candidate list");
 size_t lossy_workspace_bytes() { return kLossyBytes; }
+size_t lossy_min_workspace_bytes() { return kLossyMinBytes; }
 
 int64_t topk_chunk(int64_t n) {
   // a multiple of the tile, so that only the vector's last float4 can be partial
@@ -566,7 +574,8 @@ int64_t topk_chunk(int64_t n) {
   return c > kTopkTile ? c : kTopkTile;
 }
 
-hipError_t launch_sparsify_topk(const float* v, int64_t n, int64_t k, float* out, void* ws, hipStream_t s) {
+hipError_t launch_sparsify_topk(const float* v, int64_t n, int64_t k, float* out, void* ws, size_t ws_bytes,
+                                hipStream_t s) {
   if (n == 0) return hipSuccess;
   if (k <= 0) {
     hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks_for(n, kTile)), dim3(kThreads), 0, s, out, n);
@@ -578,7 +587,9 @@ hipError_t launch_sparsify_topk(const float* v, int64_t n, int64_t k, float* out
     hipLaunchKernelGGL(topk_small_kernel, dim3(1), dim3(kTopkThreads), 0, s, v, (int)n, kk, out);
     return hipGetLastError();
   }
+  if (ws_bytes < kLossyMinBytes) return hipErrorInvalidValue;
   TopkScratch* sc = (TopkScratch*)ws;
+  const uint32_t cap = (uint32_t)std::min<size_t>(kMaxCand, (ws_bytes - offsetof(TopkScratch, cand)) / sizeof(uint64_t));
   // one block per CU while the vector comes from the caches (each block also
   // adds its counts to the global ones), two beyond
   const unsigned most = n <= (32 << 20) ? 256 : 512;
@@ -586,13 +597,13 @@ hipError_t launch_sparsify_topk(const float* v, int64_t n, int64_t k, float* out
   hipLaunchKernelGGL(topk_init_kernel, dim3(1), block, 0, s, sc);
   hipLaunchKernelGGL(topk_count_a_kernel, g, block, 0, s, v, n, sc);
   hipLaunchKernelGGL(topk_count_b_kernel, g, block, 0, s, v, n, kk, sc);
-  hipLaunchKernelGGL(topk_split_kernel, g, block, 0, s, v, n, kk, sc, out);
-  hipLaunchKernelGGL(topk_finish_kernel, g, block, 0, s, v, n, sc, out);
+  hipLaunchKernelGGL(topk_split_kernel, g, block, 0, s, v, n, kk, cap, sc, out);
+  hipLaunchKernelGGL(topk_finish_kernel, g, block, 0, s, v, n, cap, sc, out);
   // these two return at once unless the candidates were too many
   const int64_t chunk = topk_chunk(n);
   const dim3 nchunks(blocks_for(n, chunk));
-  hipLaunchKernelGGL(topk_tie_count_kernel, nchunks, block, 0, s, v, n, chunk, sc);
-  hipLaunchKernelGGL(topk_write_kernel, nchunks, block, 0, s, v, n, chunk, (const TopkScratch*)sc, out);
+  hipLaunchKernelGGL(topk_tie_count_kernel, nchunks, block, 0, s, v, n, chunk, cap, sc);
+  hipLaunchKernelGGL(topk_write_kernel, nchunks, block, 0, s, v, n, chunk, cap, (const TopkScratch*)sc, out);
   return hipGetLastError();
 }
 

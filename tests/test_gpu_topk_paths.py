@@ -45,3 +45,27 @@ def test_candidates_around_the_list(same):
     v[at] = bits.view(np.float32) * rng.choice(np.array([-1, 1], np.float32), same)
     above = int((np.abs(v) > 5.001e-4).sum())
     _check(v, sorted({above + 1, above + same // 4 + 1, above + (3 * same) // 4 + 1, above + same}))
+
+
+def test_smallest_workspace():
+    """Workspaces of 25632 bytes, which every version has taken, hold a shorter
+    candidate list: few candidates, more than it holds, ties; quantisation too."""
+    import torch
+    dev = lambda v: torch.from_numpy(v).cuda()
+    ws = torch.empty(25632, dtype=torch.uint8, device="cuda")
+    for n in (50003, 3_000_017):
+        log(f"smallest workspace n={n}")
+        rng = np.random.default_rng(n)
+        v = rng.normal(0, 1e-3, n).astype(np.float32)
+        coarse = (v.view(np.uint32) & 0xFFFFE000).view(np.float32)     # candidates by the hundred
+        levels = np.round(v * 2e3).astype(np.float32)
+        for x in (v, coarse, levels):
+            for k in (n // 10, n // 2):
+                got = B.sparsify_topk(dev(x), k, ws=ws).cpu().numpy()
+                assert got.tobytes() == olossy.sparsify_topk(x, k).tobytes(), (n, k)
+        got = B.quantize_linear(dev(v), 8, ws=ws)[0].cpu().numpy()
+        assert np.array_equal(got, olossy.quantize_linear(v, 8)[0])
+    for call in (lambda w: B.sparsify_topk(dev(v), 5, ws=w), lambda w: B.quantize_linear(dev(v), 8, ws=w)):
+        with pytest.raises(B.LMGCError) as e:
+            call(ws[:25631])
+        assert e.value.code == -4
