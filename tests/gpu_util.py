@@ -52,3 +52,24 @@ def bf16_values(x: np.ndarray) -> np.ndarray:
     """x rounded to bfloat16 (round to nearest even), returned as float32."""
     from synth.gen import f32_to_bf16_bits, bf16_bits_to_f32
     return bf16_bits_to_f32(f32_to_bf16_bits(x))
+
+
+def graph_us(call, reps=40):
+    """Microseconds per call on the GPU alone: `reps` calls captured in a graph,
+    the fastest of some replays."""
+    import torch
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for _ in range(reps):
+            call()
+    best = float("inf")
+    for _ in range(12):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        g.replay()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / reps)
+    return best
