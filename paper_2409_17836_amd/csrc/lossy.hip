@@ -31,6 +31,7 @@ constexpr int kTopkThreads = 1024, kTopkTile = kTopkThreads * 4;
 constexpr int kBinsA = 4096, kBinsB = 2048, kBinsC = 256;
 constexpr int kShiftA = 19, kShiftB = 8;
 constexpr int kMaxChunks = 1024;        // ordered chunks of the tie passes
+constexpr int64_t kMergeMost = 128 << 10;  // elements up to which keys alike are added at once
 constexpr uint32_t kMaxCand = 1000;     // keys that share the 23-bit prefix
 
 // Scratch of a top-k call.  A and B are counted by the first two passes.  The
@@ -148,8 +149,12 @@ __global__ __launch_bounds__(kTopkThreads) void topk_init_kernel(TopkScratch* sc
 }
 
 // Adds the block's elements to hist: keys whose bits above `top` equal prefix
-// (all of them if top == 32), by their NB-valued digit at `shift`.
-template <int NB>
+// (all of them if top == 32), by their NB-valued digit at `shift`.  MERGE: a
+// thread's four keys alike are one addition (LDS atomics that meet at one
+// address run one after the other, and on short vectors of one magnitude they
+// are what a pass takes: 60000 values 33 -> 26 us a call; longer ones would pay
+// more for the comparison than they gain).
+template <int NB, bool MERGE>
 __device__ inline void count_keys(const float* __restrict__ v, int64_t n, int top, uint32_t prefix, int shift,
                                   uint32_t* __restrict__ hist) {
   __shared__ uint32_t lh[NB];
@@ -162,12 +167,15 @@ __device__ inline void count_keys(const float* __restrict__ v, int64_t n, int to
   for_each4(v, ((int64_t)blockIdx.x * kTopkThreads + threadIdx.x) * 4, stride, n,
             [&](int64_t, float4 x, int valid) __attribute__((always_inline)) {
               const float t[4] = {x.x, x.y, x.z, x.w};
+              const bool alike = MERGE && valid == 4 && mag_key(t[0]) == mag_key(t[1]) &&
+                                 mag_key(t[0]) == mag_key(t[2]) && mag_key(t[0]) == mag_key(t[3]);
+              const uint32_t add = alike ? 4u : 1u;
 #pragma unroll
               for (int e = 0; e < 4; e++) {
                 const uint32_t key = mag_key(t[e]);
-                const bool in = e < valid && (top == 32 || (key >> top) == prefix);
-                if (in && key == 0) zeros++;
-                else if (in) atomicAdd(&lh[(key >> shift) & (NB - 1)], 1u);
+                const bool in = e < (alike ? 1 : valid) && (top == 32 || (key >> top) == prefix);
+                if (in && key == 0) zeros += add;
+                else if (in) atomicAdd(&lh[(key >> shift) & (NB - 1)], add);
               }
             });
   for (int d = 32; d >= 1; d >>= 1) zeros += __shfl_xor(zeros, d);
@@ -179,15 +187,17 @@ __device__ inline void count_keys(const float* __restrict__ v, int64_t n, int to
   }
 }
 
+template <bool MERGE>
 __global__ __launch_bounds__(kTopkThreads) void topk_count_a_kernel(const float* __restrict__ v, int64_t n,
                                                                     TopkScratch* sc) {
-  count_keys<kBinsA>(v, n, 32, 0, kShiftA, sc->a);
+  count_keys<kBinsA, MERGE>(v, n, 32, 0, kShiftA, sc->a);
 }
 
+template <bool MERGE>
 __global__ __launch_bounds__(kTopkThreads) void topk_count_b_kernel(const float* __restrict__ v, int64_t n, uint32_t k,
                                                                     TopkScratch* sc) {
   const Digit a = find_digit<kBinsA>(sc->a, k);
-  count_keys<kBinsB>(v, n, kShiftA, a.d, kShiftB, sc->b);
+  count_keys<kBinsB, MERGE>(v, n, kShiftA, a.d, kShiftB, sc->b);
 }
 
 // Keeps the keys above the prefix, zeroes those below, and keeps and lists the
@@ -227,11 +237,12 @@ __global__ __launch_bounds__(kTopkThreads) void topk_split_kernel(const float* v
 // (Overlapping calls on one scratch find each other's list and its length; the
 // checks of the slot above and of the index here keep them in bounds, with
 // wrong values and no more.)
+template <bool MERGE>
 __global__ __launch_bounds__(kTopkThreads) void topk_finish_kernel(const float* v, int64_t n, uint32_t cap,
                                                                    TopkScratch* sc, float* out) {
   const uint32_t need = sc->need, count = sc->count;
   if (count > cap) {
-    count_keys<kBinsC>(v, n, kShiftB, sc->prefix, 0, sc->c);
+    count_keys<kBinsC, MERGE>(v, n, kShiftB, sc->prefix, 0, sc->c);
     return;
   }
   if (need == count) return;
@@ -348,33 +359,102 @@ __global__ __launch_bounds__(kTopkThreads) void topk_write_kernel(const float* v
   }
 }
 
+constexpr int kSmall = 8 * kTopkTile;
+
+// The bin that most of the wave's lanes hold, if that is one of two lanes' and
+// at least kCrowd hold it; kNoBin otherwise.
+constexpr int kCrowd = 12;  // (the fullest of the first digit's bins has 3 of 64 normal values)
+constexpr uint32_t kNoBin = 0xFFFFFFFFu;
+__device__ inline uint32_t crowded_bin(uint32_t bin) {
+  uint32_t hot = kNoBin;
+  int most = kCrowd - 1;
+#pragma unroll
+  for (int c = 0; c < 2; c++) {
+    const uint32_t b = __builtin_amdgcn_readlane(bin, 21 * c);
+    const int same = __popcll(__ballot(bin == b));
+    if (b != kNoBin && same > most) most = same, hot = b;
+  }
+  return hot;
+}
+
+// A thread's elements of topk_small_kernel, read again: the bin that the
+// samples crowd in is counted in a register.
+__device__ inline void count_crowded(const float* v, int n, bool sampled, uint32_t sample, uint32_t* h, int top, uint32_t prefix,
+                                     int shift, int nb) {
+  auto bin = [&](uint32_t key) __attribute__((always_inline)) {
+    return top == 32 || (key >> top) == prefix ? (key >> shift) & (nb - 1) : kNoBin;
+  };
+  const uint32_t hot = crowded_bin(sampled ? bin(sample) : kNoBin);
+  uint32_t mine = 0;
+#pragma unroll 1
+  for (int i = threadIdx.x * 4; i < n; i += kTopkTile) {
+    int valid;
+    const float4 x = load4(v, i, n, valid);
+    const float t[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const uint32_t b = e < valid ? bin(mag_key(t[e])) : kNoBin;
+      if (b == kNoBin) continue;
+      if (b == hot) mine++;
+      else atomicAdd(&h[b], 1u);
+    }
+  }
+  for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d);
+  if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&h[hot], mine);
+}
+
 // Vectors of at most kSmall values in one block: the values in registers,
 // the three digits' counts in LDS, ties ranked by a block scan per tile.  One
-// launch where the passes above are seven.
-constexpr int kSmallTiles = 8, kSmall = kSmallTiles * kTopkTile;
+// launch where the passes above are seven.  What bounds it is LDS atomics, which
+// run one after the other where they meet at one address: 32768 normal values
+// 13 us, but 97 us for zeros or a single magnitude (the passes: 23 and 33).  So
+// beyond two tiles (28 us at the worst) a wave that finds a fifth of a sample of
+// its keys in one bin of the first digit counts each digit's crowded bin in a
+// register: 31 us; the look at the sample costs the others 0.3.  TILES: 2, 4 or
+// 8, whole up to a half of them, so that few instructions are for values that
+// are not there.
+template <int TILES>
 __global__ __launch_bounds__(kTopkThreads) void topk_small_kernel(const float* v, int n, uint32_t k, float* out) {
-  constexpr int NW = kTopkThreads / 64;
+  constexpr int NW = kTopkThreads / 64, FULL = TILES > 2 ? TILES / 2 : 0;
+  constexpr bool SPREAD = TILES > 2;
   __shared__ uint32_t ha[kBinsA], hb[kBinsB], hc[kBinsC], wtot[2][NW];
   for (int i = threadIdx.x; i < kBinsA; i += kTopkThreads) ha[i] = 0;
   for (int i = threadIdx.x; i < kBinsB; i += kTopkThreads) hb[i] = 0;
   if (threadIdx.x < kBinsC) hc[threadIdx.x] = 0;
-  float x[kSmallTiles][4];
-  int valid[kSmallTiles];
+  float x[TILES][4];
+  int valid[TILES];
 #pragma unroll
-  for (int u = 0; u < kSmallTiles; u++) {
+  for (int u = 0; u < TILES; u++) {
     const int64_t i = (int64_t)u * kTopkTile + threadIdx.x * 4;
-    const float4 t = load4(v, i, n, valid[u]);
+    valid[u] = 4;  // the first FULL tiles are whole
+    const float4 t = u < FULL ? *reinterpret_cast<const float4*>(v + i) : load4(v, i, n, valid[u]);
     x[u][0] = t.x, x[u][1] = t.y, x[u][2] = t.z, x[u][3] = t.w;
   }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // one key of each lane, from four tiles and all places in a float4
+  uint32_t sample = 0;
+  bool sampled = false;
+  if constexpr (SPREAD) {
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      if ((lane & 3) == e) sample = mag_key(x[e * TILES / 4][e]), sampled = e < valid[e * TILES / 4];
+  }
+  const bool crowded = SPREAD && crowded_bin(sampled ? sample >> kShiftA : kNoBin) != kNoBin;
   __syncthreads();
   auto count = [&](uint32_t* h, int top, uint32_t prefix, int shift, int nb) __attribute__((always_inline)) {
+    if (SPREAD && __builtin_expect(crowded, 0)) {
+      count_crowded(v, n, sampled, sample, h, top, prefix, shift, nb);
+    } else {
 #pragma unroll
-    for (int u = 0; u < kSmallTiles; u++)
+      for (int u = 0; u < TILES; u++) {
+        if (SPREAD && u == 3 * TILES / 4 && u * kTopkTile >= n) break;
 #pragma unroll
-      for (int e = 0; e < 4; e++) {
-        const uint32_t key = mag_key(x[u][e]);
-        if (e < valid[u] && (top == 32 || (key >> top) == prefix)) atomicAdd(&h[(key >> shift) & (nb - 1)], 1u);
+        for (int e = 0; e < 4; e++) {
+          const uint32_t key = mag_key(x[u][e]);
+          if (e < valid[u] && (top == 32 || (key >> top) == prefix)) atomicAdd(&h[(key >> shift) & (nb - 1)], 1u);
+        }
       }
+    }
     __syncthreads();
   };
   count(ha, 32, 0, kShiftA, kBinsA);
@@ -385,10 +465,9 @@ __global__ __launch_bounds__(kTopkThreads) void topk_small_kernel(const float* v
   count(hc, kShiftB, pre, 0, kBinsC);
   const Digit c = find_digit<kBinsC>(hc, b.need);
   const uint32_t T = (pre << kShiftB) | c.d;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t running = 0;
 #pragma unroll
-  for (int u = 0; u < kSmallTiles; u++) {
+  for (int u = 0; u < TILES; u++) {
     if (u * kTopkTile >= n) break;
     uint32_t rank = 0;
     if (c.need < c.count) {  // some of the ties go
@@ -584,7 +663,10 @@ hipError_t launch_sparsify_topk(const float* v, int64_t n, int64_t k, float* out
   if (k > n) k = n;
   const uint32_t kk = (uint32_t)k;
   if (n <= kSmall) {
-    hipLaunchKernelGGL(topk_small_kernel, dim3(1), dim3(kTopkThreads), 0, s, v, (int)n, kk, out);
+    const dim3 grid(1), block(kTopkThreads);
+    if (n <= 2 * kTopkTile) hipLaunchKernelGGL(topk_small_kernel<2>, grid, block, 0, s, v, (int)n, kk, out);
+    else if (n <= 4 * kTopkTile) hipLaunchKernelGGL(topk_small_kernel<4>, grid, block, 0, s, v, (int)n, kk, out);
+    else hipLaunchKernelGGL(topk_small_kernel<8>, grid, block, 0, s, v, (int)n, kk, out);
     return hipGetLastError();
   }
   if (ws_bytes < kLossyMinBytes) return hipErrorInvalidValue;
@@ -594,11 +676,18 @@ hipError_t launch_sparsify_topk(const float* v, int64_t n, int64_t k, float* out
   // adds its counts to the global ones), two beyond
   const unsigned most = n <= (32 << 20) ? 256 : 512;
   const dim3 g(std::min(most, blocks_for(n, kTopkTile))), block(kTopkThreads);
+  const bool merge = n <= kMergeMost;
   hipLaunchKernelGGL(topk_init_kernel, dim3(1), block, 0, s, sc);
-  hipLaunchKernelGGL(topk_count_a_kernel, g, block, 0, s, v, n, sc);
-  hipLaunchKernelGGL(topk_count_b_kernel, g, block, 0, s, v, n, kk, sc);
+  if (merge) {
+    hipLaunchKernelGGL(topk_count_a_kernel<true>, g, block, 0, s, v, n, sc);
+    hipLaunchKernelGGL(topk_count_b_kernel<true>, g, block, 0, s, v, n, kk, sc);
+  } else {
+    hipLaunchKernelGGL(topk_count_a_kernel<false>, g, block, 0, s, v, n, sc);
+    hipLaunchKernelGGL(topk_count_b_kernel<false>, g, block, 0, s, v, n, kk, sc);
+  }
   hipLaunchKernelGGL(topk_split_kernel, g, block, 0, s, v, n, kk, cap, sc, out);
-  hipLaunchKernelGGL(topk_finish_kernel, g, block, 0, s, v, n, cap, sc, out);
+  if (merge) hipLaunchKernelGGL(topk_finish_kernel<true>, g, block, 0, s, v, n, cap, sc, out);
+  else hipLaunchKernelGGL(topk_finish_kernel<false>, g, block, 0, s, v, n, cap, sc, out);
   // these two return at once unless the candidates were too many
   const int64_t chunk = topk_chunk(n);
   const dim3 nchunks(blocks_for(n, chunk));

@@ -178,6 +178,7 @@ template <class T>
 T __shfl(T v, int l) {
   return cpu_hip::exchange(v, l & 63);
 }
+#define __builtin_amdgcn_readlane(v, l) __shfl(v, l)
 inline uint64_t __ballot(bool p) { return cpu_hip::ballot(p); }
 inline int __popcll(uint64_t x) { return __builtin_popcountll(x); }
 inline unsigned atomicAdd(unsigned* p, unsigned v) {

@@ -1,10 +1,10 @@
-"""Top-k against the oracle where its routes meet: the one-block kernel and the
-passes, and around the number of keys the candidate list holds (keys that
-share the threshold's leading 23 bits)."""
+"""Top-k against the oracle where its routes meet: the one-block kernel (its
+tiles, and keys that crowd in one bin) and the passes, and around the number of
+keys the candidate list holds (keys that share the threshold's leading 23 bits)."""
 import numpy as np
 import pytest
 
-from gpu_util import log
+from gpu_util import graph_us, log
 from oracle import lossy as olossy
 from paper_2409_17836_amd import binding as B
 
@@ -19,7 +19,8 @@ def _check(v, ks):
         assert got.tobytes() == olossy.sparsify_topk(v, k).tobytes(), (v.size, k)
 
 
-@pytest.mark.parametrize("n", [4096, 4097, 32764, 32768, 32769, 36000, 200001])
+@pytest.mark.parametrize("n", [4096, 4097, 8192, 8193, 16384, 16385, 24577, 32764, 32768, 32769, 36000, 131072, 131073,
+                               200001])
 def test_routes_by_size(n):
     log(f"top-k routes n={n}")
     rng = np.random.default_rng(n)
@@ -28,6 +29,35 @@ def test_routes_by_size(n):
     v[rng.random(n) < 0.7] = 0.0                     # the threshold is zero for large k
     _check(v, [n // 10, n // 2])
     _check(np.full(n, -2.5, np.float32), [1, n // 3, n])
+
+
+@pytest.mark.parametrize("n", [8193, 12287, 16385, 24577, 32767, 40001, 131071])
+def test_crowded_bins(n):
+    """One magnitude among others, keys that share the first digit or both, runs
+    of four alike, and a vector whose parts differ."""
+    log(f"top-k crowded n={n}")
+    rng = np.random.default_rng(n)
+    v = rng.normal(0, 1e-3, n).astype(np.float32)
+    clipped = np.clip(v, -7e-4, 7e-4)
+    first = (1e-3 * (1 + 0.03 * rng.random(n))).astype(np.float32)
+    both = (1e-3 * (1 + 2e-5 * rng.random(n))).astype(np.float32)
+    runs = np.repeat(v, 4)[:n]
+    parts = np.where(np.arange(n) < n // 2, v, np.float32(-3e-4)).astype(np.float32)
+    for x in (clipped, first, both, runs, parts, np.sign(v)):
+        _check(x, [1, n // 10, n // 2, n - 1])
+
+
+def test_keys_alike_cost_little_more():
+    """(With an LDS atomic for every key 97 us against 13.)"""
+    import torch
+    ws = B.workspace(B.lossy_workspace(1))
+    for n, times in ((32768, 3.5), (16385, 3.5)):
+        log(f"top-k time n={n}")
+        x = torch.randn(n, device="cuda") * 1e-3
+        out = torch.empty_like(x)
+        us = [graph_us(lambda: B.sparsify_topk(y, n // 10, out=out, ws=ws)) for y in (x, torch.zeros_like(x), x.sign())]
+        log(f"{us}")
+        assert max(us[1:]) < times * us[0], (n, us)
 
 
 @pytest.mark.parametrize("same", [1, 999, 1000, 1001, 5000])
