@@ -99,3 +99,20 @@ def test_smallest_workspace():
         with pytest.raises(B.LMGCError) as e:
             call(ws[:25631])
         assert e.value.code == -4
+
+
+def test_ranking_many_candidates_of_a_short_vector():
+    """(With no more waves than the vector has blocks for, 36 us against 17.)"""
+    import torch
+    n, same = 40000, 990
+    x = torch.randn(n, device="cuda") * 1e-3
+    few = torch.where((x.abs() - 5e-4).abs() < 1e-6, torch.zeros_like(x), x)
+    many = few.clone()
+    bits = (torch.arange(same, device="cuda", dtype=torch.int32) % 256) + (0x3A03126F & ~255)     # 5e-4
+    many[torch.arange(0, n, n // same, device="cuda")[:same]] = bits.view(torch.float32)
+    k = int((many.abs() > 5.001e-4).sum()) + same // 2
+    out, ws = torch.empty_like(x), B.workspace(B.lossy_workspace(n))
+    log("top-k ranking time")
+    us = [graph_us(lambda: B.sparsify_topk(y, k, out=out, ws=ws)) for y in (few, many)]
+    log(f"{us}")
+    assert us[1] < 1.7 * us[0], us
