@@ -446,6 +446,25 @@ int lmgc_op_gemm_bf16(const uint16_t* d_a, const uint16_t* d_b, float* d_c, int3
 enum { LMGC_OP_STORE = 0, LMGC_OP_RESID = 1, LMGC_OP_SWIGLU = 2 };
 int lmgc_op_gemm_bf16_blocked(const uint16_t* d_a, const uint16_t* d_b, void* d_out, int32_t M,
                               int32_t N, int32_t K, int32_t kind, void* stream);
+/* The same on a given tile of the output (tests compare the tiles), or on the
+ * one the library takes for the shape (tile < 0).  EINVAL for LMGC_TILE_256X128,
+ * which only the LM head has. */
+enum {
+  LMGC_TILE_32X32 = 0, LMGC_TILE_64X64 = 1, LMGC_TILE_128X64 = 2, LMGC_TILE_128X128 = 3,
+  LMGC_TILE_256X128 = 4, LMGC_TILE_256X256 = 5
+};
+int lmgc_op_gemm_bf16_tile(const uint16_t* d_a, const uint16_t* d_b, void* d_out, int32_t M,
+                           int32_t N, int32_t K, int32_t kind, int32_t tile, void* stream);
+/* The tile (LMGC_TILE_*) the library takes for a bfloat16 product of whole
+ * windows with M rows; head: the LM head's product, else any other.  N is a
+ * multiple of 256 (the model pads its weights to that).  Host.  < 0: EINVAL. */
+int32_t lmgc_gemm_tile(int32_t head, int32_t M, int32_t N, int32_t K);
+/* C[M, N] = A[M, K] * B[N, K]^T in float32, each element one chain of fused
+ * multiply-adds over rising k from +0: the float32 decoder's product, exposed
+ * for tests.  Row-major, K % 16 == 0, N % 64 == 0, pointers 16-byte aligned.
+ * GPU, async.  Errors: EINVAL. */
+int lmgc_op_gemm_f32(const float* d_a, const float* d_b, float* d_c, int32_t M, int32_t N,
+                     int32_t K, void* stream);
 /* Row-major bfloat16 [N, K] -> MFMA blocks (16 rows x 32 k per 1 KB, lane
  * order of the 16x16x32 MFMA's B operand): the layout the model keeps its
  * weights in.  N % 16 == 0, K % 32 == 0, d_dst != d_src.  GPU, async. */

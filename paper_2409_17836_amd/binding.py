@@ -102,6 +102,9 @@ def lib():
         "lmgc_container_info": (ctypes.c_int, [vp, sz, P(i64), P(i32), P(i64), P(u64)]),
         "lmgc_op_gemm_bf16": (ctypes.c_int, [vp, vp, vp, i32, i32, i32, vp]),
         "lmgc_op_gemm_bf16_blocked": (ctypes.c_int, [vp, vp, vp, i32, i32, i32, i32, vp]),
+        "lmgc_op_gemm_bf16_tile": (ctypes.c_int, [vp, vp, vp, i32, i32, i32, i32, i32, vp]),
+        "lmgc_gemm_tile": (i32, [i32, i32, i32, i32]),
+        "lmgc_op_gemm_f32": (ctypes.c_int, [vp, vp, vp, i32, i32, i32, vp]),
         "lmgc_op_block_weights": (ctypes.c_int, [vp, vp, i32, i32, vp]),
         "lmgc_op_attention_bf16": (ctypes.c_int, [vp, vp, vp, vp, i32, i32, i32, i32, i32, vp]),
         "lmgc_timing_enable": (ctypes.c_int, [i32]),
@@ -486,7 +489,26 @@ def op_gemm_bf16(a, b, c=None, stream=None):
     return c
 
 
+def op_gemm_f32(a, b, stream=None):
+    """a [M, K], b [N, K] float32 CUDA tensors -> [M, N] float32 = a b^T."""
+    import torch
+    M, K = a.shape
+    N = b.shape[0]
+    c = torch.empty((M, N), dtype=torch.float32, device=a.device)
+    _check(lib().lmgc_op_gemm_f32(_ptr(a), _ptr(b), _ptr(c), M, N, K, _stream(stream)))
+    return c
+
+
 OP_KINDS = {"store": 0, "resid": 1, "swiglu": 2}
+TILES = ["32x32", "64x64", "128x64", "128x128", "256x128", "256x256"]
+
+
+def gemm_tile(M: int, N: int, K: int, head: bool = False) -> str:
+    """The tile the library takes for a bf16 product of whole windows."""
+    t = int(lib().lmgc_gemm_tile(int(head), M, N, K))
+    if t < 0:
+        _check(t)
+    return TILES[t]
 
 
 def op_block_weights(b, stream=None):
@@ -498,18 +520,19 @@ def op_block_weights(b, stream=None):
     return out
 
 
-def op_gemm_bf16_blocked(a, b_blocked, kind: str, out=None, stream=None):
+def op_gemm_bf16_blocked(a, b_blocked, kind: str, out=None, stream=None, tile: str = None):
     """The model's blocked-weight product with its epilogue: "store" (float32
     [M, N] = a b^T), "resid" (out += a b^T; out given), "swiglu" (bf16
-    [M, N/2], b's rows gate/up interleaved in groups of 32)."""
+    [M, N/2], b's rows gate/up interleaved in groups of 32).  tile: one of
+    TILES instead of the library's choice."""
     import torch
     M, K = a.shape
     N = b_blocked.shape[0]
     if out is None:
         out = (torch.empty((M, N // 2), dtype=torch.bfloat16, device=a.device) if kind == "swiglu"
                else torch.zeros((M, N), dtype=torch.float32, device=a.device))
-    _check(lib().lmgc_op_gemm_bf16_blocked(_ptr(a), _ptr(b_blocked), _ptr(out), M, N, K, OP_KINDS[kind],
-                                           _stream(stream)))
+    _check(lib().lmgc_op_gemm_bf16_tile(_ptr(a), _ptr(b_blocked), _ptr(out), M, N, K, OP_KINDS[kind],
+                                        -1 if tile is None else TILES.index(tile), _stream(stream)))
     return out
 
 

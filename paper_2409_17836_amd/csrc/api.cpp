@@ -1219,8 +1219,14 @@ int lmgc_op_block_weights(const uint16_t* d_src, uint16_t* d_dst, int32_t N, int
   return LMGC_OK;
 }
 
-int lmgc_op_gemm_bf16_blocked(const uint16_t* d_a, const uint16_t* d_b, void* d_out, int32_t M, int32_t N,
-                              int32_t K, int32_t kind, void* stream) {
+int32_t lmgc_gemm_tile(int32_t head, int32_t M, int32_t N, int32_t K) {
+  clear_error();
+  if (M <= 0 || N <= 0 || K <= 0 || K % 64 || N % 256) return set_error(LMGC_EINVAL, "bad shape");
+  return (int32_t)pick_gemm_tile(head ? EPI_HEAD : EPI_STORE_F32, M, N, K);
+}
+
+int lmgc_op_gemm_bf16_tile(const uint16_t* d_a, const uint16_t* d_b, void* d_out, int32_t M, int32_t N,
+                           int32_t K, int32_t kind, int32_t tile, void* stream) {
   clear_error();
   if (!d_a || !d_b || !d_out || M < 0 || N <= 0 || K <= 0) return set_error(LMGC_EINVAL, "bad arguments");
   if (K % 64 || N % 256) return set_error(LMGC_EINVAL, "need K %% 64 == 0 and N %% 256 == 0");
@@ -1248,7 +1254,33 @@ int lmgc_op_gemm_bf16_blocked(const uint16_t* d_a, const uint16_t* d_b, void* d_
     default:
       return set_error(LMGC_EINVAL, "unknown kind %d", kind);
   }
-  hipError_t err = launch_gemm_bf16(d_a, d_b, M, N, K, e, (hipStream_t)stream, true);
+  if (M == 0) return LMGC_OK;
+  if (tile < 0) tile = (int32_t)pick_gemm_tile(e.kind, M, N, K);
+  if (tile > (int32_t)GemmTile::k256x256 || tile == (int32_t)GemmTile::k256x128)
+    return set_error(LMGC_EINVAL, "no tile %d for this kind", tile);
+  hipError_t err = launch_gemm_bf16_tile((GemmTile)tile, d_a, d_b, M, N, K, e, (hipStream_t)stream);
+  if (err != hipSuccess) return set_error(LMGC_EDEVICE, "gemm launch: %s", hipGetErrorString(err));
+  return LMGC_OK;
+}
+
+int lmgc_op_gemm_bf16_blocked(const uint16_t* d_a, const uint16_t* d_b, void* d_out, int32_t M, int32_t N,
+                              int32_t K, int32_t kind, void* stream) {
+  return lmgc_op_gemm_bf16_tile(d_a, d_b, d_out, M, N, K, kind, -1, stream);
+}
+
+int lmgc_op_gemm_f32(const float* d_a, const float* d_b, float* d_c, int32_t M, int32_t N, int32_t K, void* stream) {
+  clear_error();
+  if (!d_a || !d_b || !d_c || M < 0 || N <= 0 || K <= 0) return set_error(LMGC_EINVAL, "bad arguments");
+  if (K % 16 || N % 64 || M > 65535 * 64) return set_error(LMGC_EINVAL, "need K %% 16 == 0, N %% 64 == 0, M <= 65535 * 64");
+  if (((uintptr_t)d_a & 15) || ((uintptr_t)d_b & 15) || ((uintptr_t)d_c & 15))
+    return set_error(LMGC_EINVAL, "pointers must be 16-byte aligned");
+  EpiArgs e = {};
+  e.kind = EPI_STORE_F32;
+  e.M = M;
+  e.N = N;
+  e.c = d_c;
+  e.ldc = N;
+  hipError_t err = launch_gemm_f32(d_a, d_b, M, N, K, e, (hipStream_t)stream);
   if (err != hipSuccess) return set_error(LMGC_EDEVICE, "gemm launch: %s", hipGetErrorString(err));
   return LMGC_OK;
 }

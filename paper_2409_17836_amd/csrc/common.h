@@ -110,6 +110,8 @@ hipError_t launch_gemm_bf16(const uint16_t* A, const uint16_t* B, int M, int N_p
 // k256x128 only that.
 enum class GemmTile { k32x32, k64x64, k128x64, k128x128, k256x128, k256x256 };
 GemmTile pick_gemm_tile(int kind, int M, int N_pad, int K);
+hipError_t launch_gemm_bf16_tile(GemmTile t, const uint16_t* A, const uint16_t* B, int M, int N_pad, int K,
+                                 const EpiArgs& e, hipStream_t s);
 hipError_t launch_gemm_bf16_tiles(GemmTile t, const uint16_t* A, const uint16_t* B, int M, int N_pad, int K,
                                   const EpiArgs& e, hipStream_t s);
 hipError_t launch_gemm_f32(const float* A, const float* B, int M, int N_pad, int K,

@@ -591,8 +591,8 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_kernel(
 // non-temporal (they displace the activations and the K/V cache otherwise:
 // 5 to 14 % of a launch), the activation rows from L2 by every wave.
 // NB: 1 for the residual add (N = d = 4096 has only 256 blocks: one wave on
-// each CU); 2 for the kinds that pair columns c and c + 32 and for the
-// float32 store; 4, a whole 64-column group, for the head.  So a wave's
+// each CU); 2 for the kinds that pair columns c and c + 32; 4, a whole
+// 64-column group, for the head.  So a wave's
 // activation fragments serve all its blocks and the epilogue finds its
 // columns in the wave's own registers.  Against four waves of one block each
 // (two for the paired kinds) that hand their columns over through LDS, cold
@@ -842,20 +842,26 @@ hipError_t launch_gemm_bf16_rows(const uint16_t* A, const uint16_t* B, int M, in
   return launch_rows_kind<0>(A, B, M, N_pad, K, e, s);
 }
 
-hipError_t launch_gemm_bf16(const uint16_t* A, const uint16_t* B, int M, int N_pad, int K,
-                            const EpiArgs& e, hipStream_t s, bool blocked_b) {
+// B in MFMA blocks on a given tile.
+hipError_t launch_gemm_bf16_tile(GemmTile t, const uint16_t* A, const uint16_t* B, int M, int N_pad, int K,
+                                 const EpiArgs& e, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if (e.step || K % BK != 0 || N_pad % BN != 0) return hipErrorInvalidValue;
   const bool qkv = e.kind == EPI_QKV_ROPE || e.kind == EPI_QKV_BIAS;
-  if (blocked_b && (!qkv || e.hd == 128 || e.hd == 64)) {
-    const GemmTile t = pick_gemm_tile(e.kind, M, N_pad, K);
-    if (t != GemmTile::k256x256) return launch_gemm_bf16_tiles(t, A, B, M, N_pad, K, e, s);
-  }
+  if (qkv && e.hd != 128 && e.hd != 64) return hipErrorInvalidValue;
+  if (t != GemmTile::k256x256) return launch_gemm_bf16_tiles(t, A, B, M, N_pad, K, e, s);
   const int ntm = (M + BM - 1) / BM, ntn = N_pad / BN;
-  if (qkv && e.hd == 128) return launch_kind<128>(A, B, M, K, ntm, ntn, e, s, blocked_b);
-  if (qkv && e.hd == 64) return launch_kind<64>(A, B, M, K, ntm, ntn, e, s, blocked_b);
-  if (qkv) return hipErrorInvalidValue;
-  return launch_kind<0>(A, B, M, K, ntm, ntn, e, s, blocked_b);
+  if (qkv && e.hd == 128) return launch_kind<128>(A, B, M, K, ntm, ntn, e, s, true);
+  if (qkv) return launch_kind<64>(A, B, M, K, ntm, ntn, e, s, true);
+  return launch_kind<0>(A, B, M, K, ntm, ntn, e, s, true);
+}
+
+hipError_t launch_gemm_bf16(const uint16_t* A, const uint16_t* B, int M, int N_pad, int K,
+                            const EpiArgs& e, hipStream_t s, bool blocked_b) {
+  if (M <= 0) return hipSuccess;
+  if (blocked_b) return launch_gemm_bf16_tile(pick_gemm_tile(e.kind, M, N_pad, K), A, B, M, N_pad, K, e, s);
+  if (e.step || e.kind != EPI_STORE_F32 || K % BK != 0 || N_pad % BN != 0) return hipErrorInvalidValue;
+  return launch_kind<0>(A, B, M, K, (M + BM - 1) / BM, N_pad / BN, e, s, false);
 }
 
 }  // namespace lmgc

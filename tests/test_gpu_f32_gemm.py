@@ -1,7 +1,10 @@
 """The float32 decoder's matrix kernel at the edges of its 64-row and
 64-column tiles: both architectures (every epilogue), row counts around a
 tile, windows that are no multiple of four rows, vocabularies that end inside
-a tile; against the oracle, and the decoding steps bit for bit."""
+a tile; against the oracle, and the decoding steps bit for bit; and the product itself
+against the host's fused multiply-adds."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -40,3 +43,37 @@ def test_tile_edges(arch, heads, hd, ff, vocab):
         cdf2, logp2 = B.probs_stepwise(model, tok, sp)
         assert torch.equal(cdf, cdf2) and torch.equal(logp.view(torch.int32), logp2.view(torch.int32)), (W, nb)
     model.close()
+
+
+def test_product_is_one_fma_chain():
+    """Every element is acc = fmaf(a[k], b[k], acc) over rising k from +0, all
+    bits: what containers of the float32 decoder depend on.  Exponents from
+    denormal products to 2^80, signed zeros, whole rows of zeros."""
+    import torch
+    M, N, K = 65, 64, 48
+    rng = np.random.default_rng(2)
+
+    def matrix(rows):
+        x = rng.uniform(1, 2, (rows, K)) * np.exp2(rng.integers(-75, 40, (rows, K)).astype(np.float64))
+        x[: rows // 2] = rng.normal(0, 1, (rows // 2, K))
+        x[rng.random((rows, K)) < 0.05] = 0.0
+        x[3] = 0.0
+        x[4] = 1e-45 * rng.integers(0, 1000, K)
+        return (x * rng.choice([-1.0, 1.0], (rows, K))).astype(np.float32)
+
+    a, b = matrix(M), matrix(N)
+    log(f"f32 product {M}x{N}x{K} against fmaf")
+    got = B.op_gemm_f32(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()).cpu().numpy()
+    fmaf = ctypes.CDLL("libm.so.6").fmaf
+    fmaf.restype, fmaf.argtypes = ctypes.c_float, [ctypes.c_float] * 3
+    al, bl = a.tolist(), b.tolist()
+    want = np.zeros((M, N), np.float32)
+    for i in range(M):
+        for j in range(N):
+            acc = 0.0
+            for x, y in zip(al[i], bl[j]):
+                acc = fmaf(x, y, acc)
+            want[i, j] = acc
+    assert np.array_equal(got.view(np.uint32), want.view(np.uint32)), int((got.view(np.uint32) != want.view(np.uint32)).sum())
+    tiny = np.abs(want[want != 0]).min()
+    assert tiny < 1.17e-38 and np.isfinite(want).all()       # denormal results are among them

@@ -131,6 +131,19 @@ def test_quantize_constant_vector_and_errors():
             B.quantize_linear(_dev(np.ones(8, np.float32)), bits)
 
 
+@pytest.mark.parametrize("bits", [8, 16])
+def test_quantize_leaves_the_indices_of_nonfinite_values(bits):
+    import torch
+    out = torch.full((70001,), 0x5A, dtype=torch.uint8 if bits == 8 else torch.int16, device="cuda")
+    for bad in (np.nan, np.inf, -np.inf):
+        v = np.linspace(-1, 1, 70001).astype(np.float32)
+        v[69999] = bad
+        with pytest.raises(B.LMGCError) as e:
+            B.quantize_linear(_dev(v), bits, out=out)
+        assert e.value.code == -1
+        assert bool((out == 0x5A).all())
+
+
 # ------------------------------------------------------------- sign packing --
 @pytest.mark.parametrize("n", [1, 7, 8, 9, 31, 1000003])
 def test_sign_pack_sizes(n):

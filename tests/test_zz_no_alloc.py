@@ -58,3 +58,20 @@ def test_noalloc_topk_in_place_and_edges():
     assert int(z.view(torch.int32).abs().sum()) == 0
     with pytest.raises(B.LMGCError):
         B.sparsify_topk_noalloc(d, -1, d)
+
+
+@pytest.mark.parametrize("n", [33_001, 100_003, 3_000_017])
+def test_in_place_on_the_scratch(n):
+    """Vectors long enough for the passes, with more equal keys at the
+    threshold than the candidate list holds (the vector is read again after the
+    pass that usually writes it) and with few; both entry points."""
+    import torch
+    few = gen_values("laplace:1e-3", n, 14)
+    for x, k in ((_vector(n, 15), n // 10), (few, n // 10), (few, n // 2)):
+        log(f"in-place top-k: n={n} k={k}")
+        want = olossy.sparsify_topk(x, k).tobytes()
+        d = torch.from_numpy(x).cuda()
+        B.sparsify_topk_noalloc(d, k, d)
+        assert d.cpu().numpy().tobytes() == want
+        e = torch.from_numpy(x).cuda()
+        assert B.sparsify_topk(e, k, out=e).cpu().numpy().tobytes() == want
