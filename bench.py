@@ -115,7 +115,8 @@ def cpu_baseline(w, host_weights, raw_values, all_positions=256, one_positions=3
 
 # Sources of the dominant kernel: a stored traffic figure is used only while
 # they are unchanged since its counters were taken.
-KERNEL_SOURCES = ("paper_2409_17836_amd/csrc/gemm_bf16.hip", "paper_2409_17836_amd/csrc/gemm_tile.h",
+KERNEL_SOURCES = ("paper_2409_17836_amd/csrc/gemm_bf16.hip", "paper_2409_17836_amd/csrc/gemm_bf16_tiles.hip",
+                  "paper_2409_17836_amd/csrc/gemm_tile.h",
                   "paper_2409_17836_amd/csrc/epilogue.h", "paper_2409_17836_amd/csrc/common.h")
 
 

@@ -172,7 +172,10 @@ int64_t lmgc_lossy_workspace(int64_t n_values);
  *   k: number kept, 0 <= k; k >= n_values keeps everything.  The paper's
  *   "keep p percent" is k = floor(n_values * p / 100).
  * GPU, async on stream (one launch for short vectors, else a chain: two
- * counting passes and a write, and three more that only heavy ties need).
+ * counting passes, a write, a ranking of the few keys that share the
+ * threshold's leading 23 bits, and two launches that do nothing unless those
+ * are more than about 1000: many equal magnitudes, values with few mantissa
+ * bits, smooth vectors of more than some 70 million values).
  * Errors: EINVAL, ESIZE (workspace).
  */
 int lmgc_sparsify_topk(const float* d_values, int64_t n_values, int64_t k, float* d_out,

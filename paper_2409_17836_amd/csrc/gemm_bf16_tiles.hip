@@ -268,8 +268,8 @@ hipError_t launch_kind(GemmTile t, const uint16_t* A, const uint16_t* B, int M, 
 // loads, epilogue) and, per 64 of K, `one` when each CU holds one tile or
 // `two` when it holds two (the last round counts as `one` if at most a tile
 // per CU is left).  The figures (microseconds) are fits to sweeps of the
-// GPT-2, TinyLlama and 7B products over M = 8 .. 32768 on MI355X; they
-// reproduce the measured order of the tiles to within about 10 %.
+// GPT-2, TinyLlama and 7B products over M = 8 .. 32768 on MI355X; in those the
+// choice is the fastest tile or within 13 % of it.
 GemmTile pick_gemm_tile(int kind, int M, int N_pad, int K) {
   struct Row {
     GemmTile t;
